@@ -18,6 +18,14 @@ constexpr int kMaxDig = 8;     // digit sets sharing one key read (hoisting)
 constexpr int kMaxKs = 8;      // keys applied to one digit set per launch
 constexpr int kMaxMacM = 16;   // plaintext-MAC inputs per launch
 constexpr int kMaxMacK = 8;    // plaintext-MAC accumulators per launch
+// The fused middle layer's launch tables, as large as 4 KiB of kernel
+// arguments hold.  A launch after the first reads and writes all accumulators
+// and reads the digit sets again: with 64 terms a launch instead of 16,
+// (4,32,4) at N = 2^16, level 24, 512 diagonals went 4.73 -> 4.30 ms (8 fused
+// launches, now 2) and (4,16,4) at N = 2^14, level 13 0.594 -> 0.552 ms.
+constexpr int kMaxKsTerms = 64;  // terms
+constexpr int kMaxKsKeys = 32;   // keys
+constexpr int kMaxKsPts = 256;   // terms x accumulators
 
 // Per-prime constants, indexed by PQ index (special primes first).
 struct PrimeDev {
@@ -168,17 +176,17 @@ struct KsMacArgs {
   int accumulate;                    // add into the outputs
   int key_packed, f_packed;          // every key / every plaintext of the launch is packed (else none is)
   uint64_t pk_poly_bytes;            // bytes of one packed PQ polynomial
-  int key_of[kMaxMacM];
-  const uint64_t* digits[kMaxMacM];  // rotated terms: [beta][K][N]
-  const uint64_t* a[kMaxMacM];       // the add (rotated) or a_m (unrotated); Q-basis c' if pscaled
-  const uint64_t* b[kMaxMacM];       // unrotated terms: b_m
-  int pscaled[kMaxMacM];             // a (and b) are Q-basis polynomials to be multiplied by P
-  const uint64_t* key[kMaxMacM];     // [beta_max][2][kmax][N], or packed [beta_max][2] polynomials
-  uint32_t gal[kMaxMacM];            // Galois element of the key's rotation r
-  const uint64_t* f[kMaxMacK][kMaxMacM];  // null = absent diagonal
+  uint64_t pscaled;                      // bit m: term m's a (and b) are Q-basis polynomials to be multiplied by P
+  int key_of[kMaxKsTerms];
+  const uint64_t* a[kMaxKsTerms];        // the add (rotated) or a_m (unrotated); Q-basis c' if pscaled
+  const uint64_t* db[kMaxKsTerms];       // rotated terms: digits [beta][K][N]; unrotated: b_m
+  const uint64_t* key[kMaxKsKeys];       // [beta_max][2][kmax][N], or packed [beta_max][2] polynomials
+  uint32_t gal[kMaxKsKeys];              // Galois element of the key's rotation r
+  const uint64_t* f[kMaxKsPts];          // term m, accumulator k at [m nk + k]; null = absent diagonal
   uint64_t* out0[kMaxMacK];
   uint64_t* out1[kMaxMacK];
 };
+static_assert(sizeof(KsMacArgs) <= 4096 - 64, "kernel arguments");
 
 struct MacArgs {
   int nm, nk, K, prime_off;

@@ -488,12 +488,12 @@ __device__ __forceinline__ void ksmac_load(KsMacOps<NK, MB>& o, const KsMacArgs&
   // the operand structs stay in registers
   uint64_t va = 0, vb = 0;
   if (kj < 0) {
-    if (a.pscaled[m]) {
+    if (a.pscaled >> m & 1) {
       va = lq < 0 ? 0 : ld_nt(a.a[m] + (size_t)lq * n + p);
-      vb = lq < 0 ? 0 : ld_nt(a.b[m] + (size_t)lq * n + p);
+      vb = lq < 0 ? 0 : ld_nt(a.db[m] + (size_t)lq * n + p);
     } else {
       va = ld_nt(a.a[m] + off);
-      vb = ld_nt(a.b[m] + off);
+      vb = ld_nt(a.db[m] + off);
     }
   } else {
     const uint32_t src = auto_index(p, a.gal[kj], log_n);
@@ -502,8 +502,8 @@ __device__ __forceinline__ void ksmac_load(KsMacOps<NK, MB>& o, const KsMacArgs&
     // ordinary loads, kept in L2 (the keys and plaintexts stream through)
 #pragma unroll
     for (int b = 0; b < MB; ++b)
-      if (b < a.beta) o.d[b] = a.digits[m][((size_t)b * a.K + l) * n + src];
-    if (a.pscaled[m])
+      if (b < a.beta) o.d[b] = a.db[m][((size_t)b * a.K + l) * n + src];
+    if ((a.pscaled >> m & 1))
       va = lq < 0 ? 0 : a.a[m][(size_t)lq * n + src];
     else
       va = a.a[m][(size_t)l * n + src];
@@ -512,13 +512,13 @@ __device__ __forceinline__ void ksmac_load(KsMacOps<NK, MB>& o, const KsMacArgs&
   o.b = vb;
 #pragma unroll
   for (int k = 0; k < NK; ++k) {
-    const uint64_t* __restrict__ fp = a.f[k][m];
+    const uint64_t* __restrict__ fp = a.f[m * NK + k];
     o.f[k] = fp ? ld_word<FN>(reinterpret_cast<const uint8_t*>(fp) + fo, p, n) : 0;
   }
 }
 
 // The fold of one limb.  FP (primes below 2^46): operands as exact doubles,
-// every product reduced on its own (fp_mulmod_var), sums of at most 16 terms
+// every product reduced on its own (fp_mulmod_var), sums of at most 64 terms
 // of magnitude below q stay exact; about a third of the integer path's
 // instructions.  Otherwise 64 x 64 -> 128-bit products summed lazily and
 // reduced with Barrett's floor(2^128 / q).
@@ -561,7 +561,7 @@ __device__ __forceinline__ void ksmac_body(const KsMacArgs& a, const PrimeDev& p
       if (a.key_of[m] < 0) {
         av = u64_to_d(cur.a);
         bv = u64_to_d(cur.b);
-        if (a.pscaled[m]) {  // (P c0', P c1')
+        if (a.pscaled >> m & 1) {  // (P c0', P c1')
           av = fp_mulmod(av, pm, pmq, qd);
           bv = fp_mulmod(bv, pm, pmq, qd);
         }
@@ -583,7 +583,7 @@ __device__ __forceinline__ void ksmac_body(const KsMacArgs& a, const PrimeDev& p
           }
         }
         double addv = u64_to_d(cur.a);
-        if (a.pscaled[m]) addv = fp_mulmod(addv, pm, pmq, qd);
+        if (a.pscaled >> m & 1) addv = fp_mulmod(addv, pm, pmq, qd);
         // not reduced: |u| < 0.6 beta q <= 2.4 q and |addv| < q, within the
         // 4 q that fp_mulmod_var takes for its first operand
         av = u + addv;
@@ -591,7 +591,7 @@ __device__ __forceinline__ void ksmac_body(const KsMacArgs& a, const PrimeDev& p
       }
 #pragma unroll
       for (int k = 0; k < NK; ++k) {
-        if (a.f[k][m]) {
+        if (a.f[m * NK + k]) {
           const double f = u64_to_d(cur.f[k]);
           xd[k] += fp_mulmod_var(av, f, qd, qi);
           yd[k] += fp_mulmod_var(bv, f, qd, qi);
@@ -602,7 +602,7 @@ __device__ __forceinline__ void ksmac_body(const KsMacArgs& a, const PrimeDev& p
       if (a.key_of[m] < 0) {
         av = cur.a;
         bv = cur.b;
-        if (a.pscaled[m]) {  // (P c0', P c1'): zero on the special primes
+        if (a.pscaled >> m & 1) {  // (P c0', P c1'): zero on the special primes
           av = shoup(av, pr.pmod, pr.pmod_sh, q);
           bv = shoup(bv, pr.pmod, pr.pmod_sh, q);
         }
@@ -616,13 +616,13 @@ __device__ __forceinline__ void ksmac_body(const KsMacArgs& a, const PrimeDev& p
           }
         }
         uint64_t addv = cur.a;
-        if (a.pscaled[m]) addv = shoup(addv, pr.pmod, pr.pmod_sh, q);
+        if (a.pscaled >> m & 1) addv = shoup(addv, pr.pmod, pr.pmod_sh, q);
         av = add_mod(barrett128(u, q, pr.r_lo, pr.r_hi), addv, q);
         bv = barrett128(v, q, pr.r_lo, pr.r_hi);
       }
 #pragma unroll
       for (int k = 0; k < NK; ++k) {
-        if (a.f[k][m]) {
+        if (a.f[m * NK + k]) {
           add128(x[k], mul_wide(av, cur.f[k]));
           add128(y[k], mul_wide(bv, cur.f[k]));
         }
@@ -822,31 +822,30 @@ hipError_t launch_ksmac(const ckks_params* P, const KsMacArgs& a, hipStream_t s)
   // Geometry, checked before anything runs: term and accumulator counts
   // within the tables, every rotated term's key among the launch's keys and
   // consecutive with the other terms of that key, every operand present.
-  if (a.nm < 1 || a.nm > kMaxMacM || a.nk < 1 || a.nk > kMaxMacK || a.K < 1 || a.K > a.kmax || a.beta < 1 ||
-      a.beta > kMaxBeta || P->n % kKsMacAlign)
+  if (a.nm < 1 || a.nm > kMaxKsTerms || a.nk < 1 || a.nk > kMaxMacK || a.nm * a.nk > kMaxKsPts || a.K < 1 ||
+      a.K > a.kmax || a.beta < 1 || a.beta > kMaxBeta || P->n % kKsMacAlign)
     return hipErrorInvalidValue;
   int nkeys = 0, ndig = 0, nadd = 0, nunrot = 0, nf = 0;
   for (int m = 0; m < a.nm; ++m) {
     const int kj = a.key_of[m];
-    if (kj >= kMaxMacM || !a.a[m]) return hipErrorInvalidValue;
+    if (kj >= kMaxKsKeys || !a.a[m] || !a.db[m]) return hipErrorInvalidValue;
     if (kj < 0) {
-      if (!a.b[m]) return hipErrorInvalidValue;
       ++nunrot;
     } else {
-      if (!a.key[kj] || !a.digits[m]) return hipErrorInvalidValue;
+      if (!a.key[kj]) return hipErrorInvalidValue;
       for (int m2 = 0; m2 < m; ++m2)  // a key's terms are consecutive
         if (a.key_of[m2] == kj && a.key_of[m - 1] != kj) return hipErrorInvalidValue;
       bool seen_key = false, seen_dig = false, seen_add = false;
       for (int m2 = 0; m2 < m; ++m2) {
         seen_key = seen_key || a.key_of[m2] == kj;
-        seen_dig = seen_dig || (a.key_of[m2] >= 0 && a.digits[m2] == a.digits[m]);
+        seen_dig = seen_dig || (a.key_of[m2] >= 0 && a.db[m2] == a.db[m]);
         seen_add = seen_add || (a.key_of[m2] >= 0 && a.a[m2] == a.a[m]);
       }
       nkeys += !seen_key;
       ndig += !seen_dig;
       nadd += !seen_add;
     }
-    for (int k = 0; k < a.nk; ++k) nf += a.f[k][m] ? 1 : 0;
+    for (int k = 0; k < a.nk; ++k) nf += a.f[m * a.nk + k] ? 1 : 0;
   }
   for (int k = 0; k < a.nk; ++k)
     if (!a.out0[k] || !a.out1[k]) return hipErrorInvalidValue;

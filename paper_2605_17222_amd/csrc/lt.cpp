@@ -640,10 +640,12 @@ bool fuse_middle(const ckks_params* P, const ThItem& it) {
 // either unrotated (j = 0: (a_i, b_i), or (P c0', P c1') for i = 0) or the
 // middle rotation of d_i by s n1 j, formed in registers at each output
 // position and multiplied into the outputs kk right away.  Terms go to
-// launches of at most kMaxMacM terms (and so keys); the first launch writes
-// the outputs, later ones add into them.  Diagonals given as slot vectors
-// are encoded right before the launch that reads them (f^ = encode(rot(z,
-// -G_k))), into workspace the next launch reuses.
+// launches of as many terms as the launch tables hold; the first launch
+// writes the outputs, later ones add into them, so every launch saved saves a
+// pass over the accumulators and one over the digit sets.  Diagonals given as
+// slot vectors are encoded right before the launch that reads them (f^ =
+// encode(rot(z, -G_k))), into workspace the next launch reuses; their
+// launches stay at kMaxMacM terms, which bounds that workspace.
 void ksmac(Run& R, ThItem& it, const std::vector<int>& kk) {
   const ckks_params* P = R.P;
   const int inner = it.n1 * it.n2;
@@ -654,6 +656,7 @@ void ksmac(Run& R, ThItem& it, const std::vector<int>& kk) {
   for (int j = 0; j < it.n2; ++j)
     for (int i = 0; i < it.n1; ++i)
       if (it.used_m[it.n1 * j + i]) terms.push_back(Term{it.n1 * j + i, j, i});
+  const int max_nm = it.D.z ? kMaxMacM : std::min(kMaxKsTerms, kMaxKsPts / (int)kk.size());
   bool first = true;
   size_t t0 = 0;
   while (t0 < terms.size()) {
@@ -671,14 +674,15 @@ void ksmac(Run& R, ThItem& it, const std::vector<int>& kk) {
     const size_t mark = R.ws.mark();
     std::vector<EncItem> enc;
     size_t t = t0;
-    for (; t < terms.size() && a.nm < kMaxMacM; ++t) {
+    for (; t < terms.size() && a.nm < max_nm; ++t) {
       const Term& tm = terms[t];
       const int m = a.nm;
+      if (tm.j != 0 && tm.j != last_j && nkeys == kMaxKsKeys) break;
       if (tm.j == 0) {
         a.key_of[m] = -1;
         a.a[m] = tm.i == 0 ? it.c0 : it.A[tm.i];
-        a.b[m] = tm.i == 0 ? it.c1 : it.B[tm.i];
-        a.pscaled[m] = tm.i == 0 ? 1 : 0;
+        a.db[m] = tm.i == 0 ? it.c1 : it.B[tm.i];
+        a.pscaled |= (uint64_t)(tm.i == 0) << m;
       } else {
         if (tm.j != last_j) {
           const long r = it.stride * it.n1 * tm.j;
@@ -688,20 +692,21 @@ void ksmac(Run& R, ThItem& it, const std::vector<int>& kk) {
           last_j = tm.j;
         }
         a.key_of[m] = nkeys - 1;
-        a.digits[m] = it.Dg[tm.i];
+        a.db[m] = it.Dg[tm.i];
         a.a[m] = tm.i == 0 ? it.c0 : it.A[tm.i];
-        a.pscaled[m] = tm.i == 0 ? 1 : 0;
+        a.pscaled |= (uint64_t)(tm.i == 0) << m;
       }
       for (size_t k = 0; k < kk.size(); ++k) {
         const int idx = kk[k] * inner + tm.m;
-        a.f[k][m] = nullptr;
+        const uint64_t*& f = a.f[m * kk.size() + k];
+        f = nullptr;
         if (kk[k] < 0 || !it.D.has(idx)) continue;
         if (it.D.z) {
           uint64_t* buf = R.limbs(a.K);
           enc.push_back(EncItem{it.D.z[idx], -it.giant(P, kk[k]), it.D.zscale, 0, a.K, buf, nullptr});
-          a.f[k][m] = buf;
+          f = buf;
         } else {
-          a.f[k][m] = it.D.pt[idx];
+          f = it.D.pt[idx];
         }
       }
       ++a.nm;

@@ -124,3 +124,28 @@ def test_fused_many_accumulators_every_limb_kind_packed():
     assert np.array_equal(_single(c, split, dpts, pkeys, dct), ref)
     assert np.array_equal(_single(c, split, ppts, pkeys, dct), ref)
     assert np.array_equal(_single(c, split, ppts, dkeys, dct), ref)
+
+
+@pytest.mark.parametrize("split,drop", [((1, 33, 2), 0), ((1, 34, 2), 5), ((2, 33, 2), 0), ((4, 17, 4), 0),
+                                        ((4, 17, 3), 4), ((3, 12, 2), 7)])
+def test_fused_launch_table_edges(case, split, drop):
+    """Launches at the edges of the launch tables (32 keys, 64 terms, one more
+    of either), inner steps of 1 to 4, with every diagonal and with every
+    drop-th one absent, against the oracle's Algorithm 2, plain and packed."""
+    log("fused launch tables", split, drop)
+    c = case
+    o, prm = c["o"], c["prm"]
+    n = split[0] * split[1] * split[2]
+    diags = {d: z for d, z in W.banded_diagonals(47, prm.slots, range(n)).items() if not drop or d % drop}
+    pts = o.th_plaintexts(diags, *split, c["delta"])
+    keys = _keys(c, split)
+    ref = o.lt_th(c["level"], c["ct"], split, pts, keys)
+    dpts = [None if f is None else H.to_device(f) for f in pts]
+    dkeys = {r: H.to_device(k) for r, k in keys.items()}
+    dct = [H.to_device(c["ct"][0]), H.to_device(c["ct"][1])]
+    assert np.array_equal(_single(c, split, dpts, dkeys, dct), ref)
+    P = gpu_params(prm)
+    pkeys = {r: H.ckks_pack(P, k) for r, k in dkeys.items()}
+    ppts = [None if f is None else H.ckks_pack(P, f) for f in dpts]
+    assert np.array_equal(_single(c, split, ppts, pkeys, dct), ref)
+    assert np.array_equal(_single(c, split, dpts, pkeys, dct), ref)
