@@ -44,7 +44,7 @@ PROFILE_LTS = 60  # TH-BSGS LTs in those runs: `--profile-only --only th --steps
 # The library's kernels of Algorithm 2's key-switch phases (lines 4-5, 8-14
 # fused with the multiply-accumulate, 17-18)
 KEYSWITCH_KERNELS = ("keyswitch", "ksmac", "keyswitch_gather")
-TH444_KERNEL = {"keyswitch_gather": "ks_gather_kernel<false, 3>", "ksmac": "ksmac_kernel<4, 3, false, false>"}
+TH444_KERNEL = {"keyswitch_gather": "ks_gather_kernel<false, 3>", "ksmac": "ksmac_kernel<4, 3, true, false, false>"}
 
 
 def parse():

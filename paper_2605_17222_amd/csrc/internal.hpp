@@ -44,7 +44,8 @@ struct PrimeDev {
   double ninv_d, ninv_q;   // N^-1 mod q as a double and divided by q
   uint64_t pk_off;         // byte offset of this limb in a packed PQ polynomial
   int narrow;              // q < 2^40: packed as a 32-bit and an 8-bit plane
-  int pk_pad;
+  int bs_shift;            // bits(q) - 1 and floor(2^(64 + bs_shift) / q): barrett_sum
+  uint64_t bs_mu;
 };
 
 // Packed storage of resident operands (keys, plaintexts): a limb of a prime
@@ -164,25 +165,26 @@ struct KsGatherArgs {
 };
 
 // Lines 8-14 of Algorithm 2 in one pass (middle key switch fused with the
-// plaintext multiply-accumulate).  Term m is either unrotated, (a_m, b_m)
-// read at the output position (key_of[m] < 0), or the middle rotation of
-// digit set digits[m] by key key_of[m]: at output position p the product
-// <d, swk> and the add a[m] are formed at auto_index(p, gal[key]), so the
-// rotated (a_m, b_m) exist only in registers.  Terms sharing a key are
-// consecutive.
+// plaintext multiply-accumulate).  First nu unrotated terms, (a_m, b_m) read
+// at the output position; then nr rotated ones in groups of ni that share a
+// key (group g: key[g], gal[g]): at output position p the product <d, swk>
+// and the add a[m] are formed at auto_index(p, gal[g]), so the rotated
+// (a_m, b_m) exist only in registers.  Every pointer of a term is readable:
+// an absent plaintext's entry repeats a present one of the term and its meta
+// bit is clear.
 constexpr int kKsMacAlign = 2048;  // N must be a multiple: 256 threads per workgroup x 8 XCDs
+constexpr uint32_t kKsMacPscaled = 1u << 8;  // meta: a (and b) are Q-basis polynomials to be multiplied by P
 struct KsMacArgs {
-  int nm, nk, K, beta, kmax;
+  int nu, nr, ni, nk, K, beta, kmax;
   int accumulate;                    // add into the outputs
   int key_packed, f_packed;          // every key / every plaintext of the launch is packed (else none is)
   uint64_t pk_poly_bytes;            // bytes of one packed PQ polynomial
-  uint64_t pscaled;                      // bit m: term m's a (and b) are Q-basis polynomials to be multiplied by P
-  int key_of[kMaxKsTerms];
-  const uint64_t* a[kMaxKsTerms];        // the add (rotated) or a_m (unrotated); Q-basis c' if pscaled
-  const uint64_t* db[kMaxKsTerms];       // rotated terms: digits [beta][K][N]; unrotated: b_m
-  const uint64_t* key[kMaxKsKeys];       // [beta_max][2][kmax][N], or packed [beta_max][2] polynomials
-  uint32_t gal[kMaxKsKeys];              // Galois element of the key's rotation r
-  const uint64_t* f[kMaxKsPts];          // term m, accumulator k at [m nk + k]; null = absent diagonal
+  uint32_t meta[kMaxKsTerms];        // bit k: accumulator k has a plaintext; kKsMacPscaled
+  const uint64_t* a[kMaxKsTerms];    // the add (rotated) or a_m (unrotated)
+  const uint64_t* db[kMaxKsTerms];   // rotated terms: digits [beta][K][N]; unrotated: b_m
+  const uint64_t* key[kMaxKsKeys];   // [beta_max][2][kmax][N], or packed [beta_max][2] polynomials
+  uint32_t gal[kMaxKsKeys];          // Galois element of the key's rotation r
+  const uint64_t* f[kMaxKsPts];      // term m, accumulator k at [m nk + k]
   uint64_t* out0[kMaxMacK];
   uint64_t* out1[kMaxMacK];
 };

@@ -656,13 +656,24 @@ void ksmac(Run& R, ThItem& it, const std::vector<int>& kk) {
   for (int j = 0; j < it.n2; ++j)
     for (int i = 0; i < it.n1; ++i)
       if (it.used_m[it.n1 * j + i]) terms.push_back(Term{it.n1 * j + i, j, i});
-  const int max_nm = it.D.z ? kMaxMacM : std::min(kMaxKsTerms, kMaxKsPts / (int)kk.size());
+  const int nk = (int)kk.size();
+  size_t nu = 0;  // unrotated terms, first
+  while (nu < terms.size() && terms[nu].j == 0) ++nu;
+  // An even number n1 of terms reads its key once if every rotation has all
+  // of its terms; otherwise each term reads its own (from L2 after the first).
+  int ni = it.n1 % 2 == 0 && it.n1 <= kMaxMacM / 2 && (int)nu == it.n1 && it.ks->packed == (it.D.packed && !it.D.z) ? it.n1 : 1;
+  std::vector<int> per_j(it.n2, 0);
+  for (const Term& t : terms) ++per_j[t.j];
+  for (int c : per_j)
+    if (c != 0 && c != it.n1) ni = 1;
+  const int max_nm = it.D.z ? kMaxMacM : std::min(kMaxKsTerms, kMaxKsPts / nk);
   bool first = true;
   size_t t0 = 0;
   while (t0 < terms.size()) {
     KsMacArgs a;
     memset(&a, 0, sizeof(a));
-    a.nk = (int)kk.size();
+    a.nk = nk;
+    a.ni = ni;
     a.K = P->K(it.level);
     a.beta = P->beta(it.level);
     a.kmax = P->Kmax();
@@ -670,46 +681,40 @@ void ksmac(Run& R, ThItem& it, const std::vector<int>& kk) {
     a.key_packed = it.ks->packed ? 1 : 0;
     a.f_packed = it.D.packed && !it.D.z ? 1 : 0;  // encoded plaintexts are written unpacked
     a.pk_poly_bytes = P->pk_poly_bytes;
-    int nkeys = 0, last_j = -1;
     const size_t mark = R.ws.mark();
     std::vector<EncItem> enc;
     size_t t = t0;
-    for (; t < terms.size() && a.nm < max_nm; ++t) {
+    for (; t < terms.size(); ++t) {
       const Term& tm = terms[t];
-      const int m = a.nm;
-      if (tm.j != 0 && tm.j != last_j && nkeys == kMaxKsKeys) break;
-      if (tm.j == 0) {
-        a.key_of[m] = -1;
-        a.a[m] = tm.i == 0 ? it.c0 : it.A[tm.i];
-        a.db[m] = tm.i == 0 ? it.c1 : it.B[tm.i];
-        a.pscaled |= (uint64_t)(tm.i == 0) << m;
-      } else {
-        if (tm.j != last_j) {
-          const long r = it.stride * it.n1 * tm.j;
-          a.key[nkeys] = it.ks->get(R, r);
-          a.gal[nkeys] = galois(P, r);
-          ++nkeys;
-          last_j = tm.j;
-        }
-        a.key_of[m] = nkeys - 1;
-        a.db[m] = it.Dg[tm.i];
-        a.a[m] = tm.i == 0 ? it.c0 : it.A[tm.i];
-        a.pscaled |= (uint64_t)(tm.i == 0) << m;
+      const int m = a.nu + a.nr;
+      const bool group = tm.j == 0 || a.nr % ni == 0;  // a whole group fits, or none of it
+      if (m + (tm.j == 0 || !group ? 1 : ni) > max_nm) break;
+      if (tm.j != 0 && group) {
+        if (a.nr / ni == kMaxKsKeys) break;
+        const long r = it.stride * it.n1 * tm.j;
+        a.key[a.nr / ni] = it.ks->get(R, r);
+        a.gal[a.nr / ni] = galois(P, r);
       }
-      for (size_t k = 0; k < kk.size(); ++k) {
+      a.a[m] = tm.i == 0 ? it.c0 : it.A[tm.i];
+      a.db[m] = tm.j != 0 ? it.Dg[tm.i] : (tm.i == 0 ? it.c1 : it.B[tm.i]);
+      if (tm.i == 0) a.meta[m] |= kKsMacPscaled;
+      const uint64_t* any = nullptr;
+      for (int k = 0; k < nk; ++k) {
         const int idx = kk[k] * inner + tm.m;
-        const uint64_t*& f = a.f[m * kk.size() + k];
-        f = nullptr;
         if (kk[k] < 0 || !it.D.has(idx)) continue;
         if (it.D.z) {
           uint64_t* buf = R.limbs(a.K);
           enc.push_back(EncItem{it.D.z[idx], -it.giant(P, kk[k]), it.D.zscale, 0, a.K, buf, nullptr});
-          f = buf;
+          any = buf;
         } else {
-          f = it.D.pt[idx];
+          any = it.D.pt[idx];
         }
+        a.f[m * nk + k] = any;
+        a.meta[m] |= 1u << k;
       }
-      ++a.nm;
+      for (int k = 0; k < nk; ++k)  // a used term has a diagonal; absent ones repeat it, masked
+        if (!(a.meta[m] >> k & 1)) a.f[m * nk + k] = any;
+      ++(tm.j == 0 ? a.nu : a.nr);
     }
     for (size_t k = 0; k < kk.size(); ++k) {
       a.out0[k] = kk[k] >= 0 ? it.U0[kk[k]] : it.acc0;

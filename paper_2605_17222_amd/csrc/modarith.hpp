@@ -75,6 +75,58 @@ __host__ __device__ __forceinline__ uint64_t barrett128(U128 x, uint64_t q, uint
   return csub(x.lo - qhat * q, q);
 }
 
+#ifdef __HIP_DEVICE_COMPILE__
+// acc += a b for a, b < 2^61 (the cross products' sum stays below 2^63):
+// four multiply-adds and one carry chain, against fifteen instructions for
+// mul_wide and add128.
+__device__ __forceinline__ void mac128(U128& acc, uint64_t a, uint64_t b) {
+  const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32);
+  const uint32_t b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
+  uint64_t m = (uint64_t)a0 * b1;
+  m += (uint64_t)a1 * b0;
+  const uint64_t hi = acc.hi + (uint64_t)a1 * b1;
+  uint64_t lo = acc.lo, c, d;
+  asm("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(lo), "=s"(c) : "v"(a0), "v"(b0));
+  uint32_t mh, w1, w2, w3;
+  asm("v_addc_co_u32_e64 %0, %1, 0, %2, %3" : "=v"(mh), "=s"(d) : "v"((uint32_t)(m >> 32)), "s"(c));
+  asm("v_add_co_u32_e64 %0, %1, %2, %3" : "=v"(w1), "=s"(c) : "v"((uint32_t)(lo >> 32)), "v"((uint32_t)m));
+  asm("v_addc_co_u32_e64 %0, %1, %2, %3, %4" : "=v"(w2), "=s"(d) : "v"((uint32_t)hi), "v"(mh), "s"(c));
+  asm("v_addc_co_u32_e64 %0, %1, 0, %2, %3" : "=v"(w3), "=s"(c) : "v"((uint32_t)(hi >> 32)), "s"(d));
+  acc.lo = (uint32_t)lo | ((uint64_t)w1 << 32);
+  acc.hi = w2 | ((uint64_t)w3 << 32);
+}
+#else
+__host__ __device__ __forceinline__ void mac128(U128& acc, uint64_t a, uint64_t b) { add128(acc, mul_wide(a, b)); }
+#endif
+
+// a b / 2^64 rounded down, or one less: the low partial product and its carry
+// are left out.
+__host__ __device__ __forceinline__ uint64_t mulhi64_under(uint64_t a, uint64_t b) {
+  const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32);
+  const uint32_t b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
+#ifdef __HIP_DEVICE_COMPILE__
+  uint64_t m = (uint64_t)a0 * b1, c;
+  asm("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(m), "=s"(c) : "v"(a1), "v"(b0));
+  uint32_t ch;
+  asm("v_cndmask_b32_e64 %0, 0, 1, %1" : "=v"(ch) : "s"(c));
+#else
+  uint64_t m;
+  const uint32_t ch = __builtin_add_overflow((uint64_t)a0 * b1, (uint64_t)a1 * b0, &m) ? 1 : 0;
+#endif
+  return (uint64_t)a1 * b1 + ((m >> 32) | ((uint64_t)ch << 32));
+}
+
+// x mod q for a sum x of at most 4 products of residues (x < 4 q^2, q < 2^61):
+// with s = bits(q) - 1, x / 2^s < 2^64 and mu = floor(2^(64+s) / q) < 2^64, and
+// qhat = (x >> s) mu / 2^64 falls short of x / q by less than 1 (the shift)
+// + 1 (mu) + 2 (mulhi64_under), so x - qhat q is in [0, 4q).
+__host__ __device__ __forceinline__ uint64_t barrett_sum(U128 x, uint64_t q, uint64_t mu, int s) {
+  const uint64_t xh = (x.lo >> s) | (x.hi << 1 << (63 - s));
+  uint64_t r = x.lo - mulhi64_under(xh, mu) * q;
+  r = csub(r, 2 * q);
+  return csub(r, q);
+}
+
 // ---- exact FP64 arithmetic for primes q < 2^46 ----------------------------
 // Residues are doubles holding exact integers.  A product x*w (0 <= w < q) is
 // reduced with an FMA two-product, so the remainder is exact:
