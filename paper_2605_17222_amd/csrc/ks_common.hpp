@@ -16,7 +16,7 @@ constexpr int kThreads = 256;
 // stored non-temporally too: measured, that speeds up the reader (the MAC
 // by about 8%).  The gather's accumulators, which the ModDown that follows
 // reads right away, use ordinary stores.
-__device__ __forceinline__ uint64_t ld_nt(const uint64_t* p) { return __builtin_nontemporal_load(p); }
+__device__ __forceinline__ uint64_t ld_nt(const uint64_t* p) { return __builtin_nontemporal_load(glb(p)); }
 
 // Bytes between the polynomials of a key [beta_max][2] (index 2 b + s):
 // packed polynomials of pk_bytes each, or [kmax][N] words each.

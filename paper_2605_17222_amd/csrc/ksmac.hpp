@@ -31,6 +31,12 @@ static_assert(kKsMacAlign == kThreads * kXcds, "ksmac grid: whole workgroups per
 // (a pointer load and its wait each): (4,4,4) 439 -> 397 us, (4,32,4) 3.31 ->
 // 2.78 ms, (1,16,4) 580 -> 581, packed 530 -> 486; (4,16,4) at N = 2^14,
 // level 13, 318 (with 16 terms a launch) -> 197 us.
+
+// The launch's arguments where they are, in the kernel-argument segment: read
+// through a by-value parameter, kernels with more than 6 accumulators copied all
+// of them into per-lane scratch (3.9 KB a lane).
+typedef const __attribute__((address_space(4))) KsMacArgs KsMacArgsK;
+
 template <int NK, int MB>
 struct KsMacTerm {
   uint64_t d[MB], a, f[NK];
@@ -49,7 +55,7 @@ struct KsMacWhere {
 };
 
 template <int NK, bool FN>
-__device__ __forceinline__ void ksmac_load_f(uint64_t (&f)[NK], const KsMacArgs& a, int m, uint32_t p, size_t n,
+__device__ __forceinline__ void ksmac_load_f(uint64_t (&f)[NK], KsMacArgsK& a, int m, uint32_t p, size_t n,
                                              const KsMacWhere& w, bool live) {
 #pragma unroll
   for (int k = 0; k < NK; ++k)
@@ -60,17 +66,17 @@ __device__ __forceinline__ void ksmac_load_f(uint64_t (&f)[NK], const KsMacArgs&
 // launch's other rotations read them again, from this XCD's L2), plaintexts
 // at p (non-temporal).  !live: past the last term.
 template <int NK, int MB, bool FN>
-__device__ __forceinline__ void ksmac_load(KsMacTerm<NK, MB>& o, const KsMacArgs& a, int m, uint32_t src, uint32_t p,
+__device__ __forceinline__ void ksmac_load(KsMacTerm<NK, MB>& o, KsMacArgsK& a, int m, uint32_t src, uint32_t p,
                                            size_t n, const KsMacWhere& w, bool live) {
-  const uint64_t* __restrict__ d = a.db[m] + (live ? w.lo : 0);
+  const CKKS_GLOBAL uint64_t* __restrict__ d = glb(a.db[m]) + (live ? w.lo : 0);
 #pragma unroll
   for (int b = 0; b < MB; ++b) o.d[b] = d[b * w.dn + (live ? src : 0)];
-  o.a = (a.a[m] + (live ? (a.meta[m] & kKsMacPscaled ? w.lqo : w.lo) : 0))[live ? src : 0];
+  o.a = (glb(a.a[m]) + (live ? (a.meta[m] & kKsMacPscaled ? w.lqo : w.lo) : 0))[live ? src : 0];
   ksmac_load_f<NK, FN>(o.f, a, m, p, n, w, live);
 }
 
 template <int MB, bool KN>
-__device__ __forceinline__ void ksmac_load_key(KsMacKey<MB>& o, const KsMacArgs& a, int g, uint32_t src, size_t n,
+__device__ __forceinline__ void ksmac_load_key(KsMacKey<MB>& o, KsMacArgsK& a, int g, uint32_t src, size_t n,
                                                const KsMacWhere& w, bool live) {
   const uint8_t* b = reinterpret_cast<const uint8_t*>(a.key[g]) + (live ? w.ko : 0);
 #pragma unroll
@@ -195,7 +201,7 @@ struct KsMacFoldInt {
 // 8-bit planes).  GROUPED: an even number a.ni of rotated terms per key, else
 // one.
 template <int NK, int MB, bool GROUPED, bool PK, bool PF, bool NARROW, typename Fold>
-__device__ __forceinline__ void ksmac_body(const KsMacArgs& a, const PrimeDev& pr, int l, uint32_t p, size_t n,
+__device__ __forceinline__ void ksmac_body(KsMacArgsK& a, const PrimeDev& pr, int l, uint32_t p, size_t n,
                                            int log_n, int alpha) {
   constexpr bool KN = PK && NARROW, FN = PF && NARROW;
   KsMacWhere w;
@@ -294,11 +300,11 @@ __device__ __forceinline__ void ksmac_body(const KsMacArgs& a, const PrimeDev& p
   for (int k = 0; k < NK; ++k) {
     uint64_t xr = F.out0(k), yr = F.out1(k);
     if (a.accumulate) {
-      xr = add_mod(xr, a.out0[k][off], pr.q);
-      yr = add_mod(yr, a.out1[k][off], pr.q);
+      xr = add_mod(xr, glb(a.out0[k])[off], pr.q);
+      yr = add_mod(yr, glb(a.out1[k])[off], pr.q);
     }
-    __builtin_nontemporal_store(xr, a.out0[k] + off);
-    __builtin_nontemporal_store(yr, a.out1[k] + off);
+    __builtin_nontemporal_store(xr, glb(a.out0[k]) + off);
+    __builtin_nontemporal_store(yr, glb(a.out1[k]) + off);
   }
 }
 
@@ -314,7 +320,8 @@ __device__ __forceinline__ void ksmac_body(const KsMacArgs& a, const PrimeDev& p
 // limb (prime below 2^40, so on the FP64 path) is read from its planes.
 template <int NK, int MB, bool GROUPED, bool PK, bool PF>
 __global__ void __launch_bounds__(kThreads)
-    ksmac_kernel(KsMacArgs a, const PrimeDev* __restrict__ primes, int log_n, int alpha) {
+    ksmac_kernel(KsMacArgs, const PrimeDev* __restrict__ primes, int log_n, int alpha) {
+  KsMacArgsK& a = *(KsMacArgsK*)__builtin_amdgcn_kernarg_segment_ptr();  // the first argument
   const uint32_t p = ((blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds) * kThreads + threadIdx.x;
   const int l = (int)blockIdx.y;
   const PrimeDev& pr = primes[l];
@@ -325,14 +332,6 @@ __global__ void __launch_bounds__(kThreads)
     if constexpr (PK || PF) {
       if (pr.narrow) {
         ksmac_body<NK, MB, GROUPED, PK, PF, true, Fp>(a, pr, l, p, n, log_n, alpha);
-        return;
-      }
-      // With more than 6 accumulators, three bodies in one kernel make the
-      // compiler keep the whole argument block in per-lane scratch; the wide
-      // limbs of the FP64 path (primes between 2^40 and 2^46) then take the
-      // integer body, which serves any prime.
-      if constexpr (NK > 6) {
-        ksmac_body<NK, MB, GROUPED, PK, PF, false, Int>(a, pr, l, p, n, log_n, alpha);
         return;
       }
     }

@@ -75,11 +75,11 @@ __host__ __device__ __forceinline__ uint64_t barrett128(U128 x, uint64_t q, uint
   return csub(x.lo - qhat * q, q);
 }
 
-#ifdef __HIP_DEVICE_COMPILE__
 // acc += a b for a, b < 2^61 (the cross products' sum stays below 2^63):
 // four multiply-adds and one carry chain, against fifteen instructions for
 // mul_wide and add128.
-__device__ __forceinline__ void mac128(U128& acc, uint64_t a, uint64_t b) {
+__host__ __device__ __forceinline__ void mac128(U128& acc, uint64_t a, uint64_t b) {
+#ifdef __HIP_DEVICE_COMPILE__
   const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32);
   const uint32_t b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
   uint64_t m = (uint64_t)a0 * b1;
@@ -94,10 +94,10 @@ __device__ __forceinline__ void mac128(U128& acc, uint64_t a, uint64_t b) {
   asm("v_addc_co_u32_e64 %0, %1, 0, %2, %3" : "=v"(w3), "=s"(c) : "v"((uint32_t)(hi >> 32)), "s"(d));
   acc.lo = (uint32_t)lo | ((uint64_t)w1 << 32);
   acc.hi = w2 | ((uint64_t)w3 << 32);
-}
 #else
-__host__ __device__ __forceinline__ void mac128(U128& acc, uint64_t a, uint64_t b) { add128(acc, mul_wide(a, b)); }
+  add128(acc, mul_wide(a, b));
 #endif
+}
 
 // a b / 2^64 rounded down, or one less: the low partial product and its carry
 // are left out.
@@ -235,17 +235,22 @@ template <typename PrimeT>
 __device__ __forceinline__ LimbRef limb_ref(const void* poly, int l, size_t n, bool packed, const PrimeT& pr) {
   return {reinterpret_cast<const uint8_t*>(poly) + limb_off(l, n, packed, pr), packed && pr.narrow};
 }
+// Global memory, said in the pointer's type: a pointer out of a table that the
+// compiler cannot trace would otherwise be read by flat loads.
+#define CKKS_GLOBAL __attribute__((address_space(1)))
+__device__ __forceinline__ const CKKS_GLOBAL uint64_t* glb(const uint64_t* p) { return (const CKKS_GLOBAL uint64_t*)p; }
+__device__ __forceinline__ CKKS_GLOBAL uint64_t* glb(uint64_t* p) { return (CKKS_GLOBAL uint64_t*)p; }
 // Word p of a limb; non-temporal loads, these operands are read once per launch.
 template <bool NARROW>
 __device__ __forceinline__ uint64_t ld_word(const uint8_t* b, size_t p, size_t n) {
   if constexpr (NARROW) {
-    const uint8_t* c = b + (p / kPackChunk) * (5 * kPackChunk);
+    const CKKS_GLOBAL uint8_t* c = (const CKKS_GLOBAL uint8_t*)b + (p / kPackChunk) * (5 * kPackChunk);
     const size_t r = p % kPackChunk;
-    const uint64_t lo = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(c) + r);
+    const uint64_t lo = __builtin_nontemporal_load((const CKKS_GLOBAL uint32_t*)c + r);
     const uint64_t hi = __builtin_nontemporal_load(c + 4 * kPackChunk + r);
     return lo | (hi << 32);
   } else {
-    return __builtin_nontemporal_load(reinterpret_cast<const uint64_t*>(b) + p);
+    return __builtin_nontemporal_load((const CKKS_GLOBAL uint64_t*)b + p);
   }
 }
 #endif
