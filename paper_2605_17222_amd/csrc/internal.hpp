@@ -57,6 +57,9 @@ constexpr uint64_t kNarrowLimit = 1ull << 40;
 
 constexpr uint64_t kFpPrimeLimit = 1ull << 46;
 
+// Transforms of at most 2^13 words run in one kernel, larger ones in two passes.
+__host__ __device__ inline bool ntt_one_kernel(int log_n) { return log_n <= 13; }
+
 // The two NTT passes split log2 N = (log2 N - B) + B: the column pass does the
 // first log2 N - B stages, the row pass the last B.
 __host__ __device__ inline int ntt_row_log(int log_n) { return log_n / 2; }
@@ -110,6 +113,10 @@ struct LimbRange {
 constexpr int kMaxRanges = 32;
 struct NttArgs {
   int nr = 0;
+  // Set by the launch: where each range starts in the sequence of limbs, or
+  // every range covers the same primes and they are taken prime by prime.
+  int interleave = 0;
+  int start[kMaxRanges];
   LimbRange r[kMaxRanges];
 };
 

@@ -116,6 +116,31 @@ __host__ __device__ __forceinline__ uint64_t mulhi64_under(uint64_t a, uint64_t 
   return (uint64_t)a1 * b1 + ((m >> 32) | ((uint64_t)ch << 32));
 }
 
+// x + a w - qhat q (mod 2^64) with qhat = mulhi64_under(a, wp): adds
+// a w mod q to x lazily.  With wp = floor(w 2^64 / q) the Shoup remainder
+// a w - floor(a wp / 2^64) q is below q (1 + a / 2^64), so what is added is in
+// [0, 3q) for any a < 2^64.
+__host__ __device__ __forceinline__ uint64_t shoup_add(uint64_t x, uint64_t a, uint64_t w, uint64_t wp, uint64_t q) {
+  const uint64_t h = mulhi64_under(a, wp), nq = 0 - q;
+  const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32), w0 = (uint32_t)w, w1 = (uint32_t)(w >> 32);
+  const uint32_t h0 = (uint32_t)h, h1 = (uint32_t)(h >> 32), n0 = (uint32_t)nq, n1 = (uint32_t)(nq >> 32);
+  uint64_t r = (uint64_t)a0 * w0 + x;
+  r += (uint64_t)h0 * n0;
+  const uint32_t hi = (uint32_t)(r >> 32) + a0 * w1 + a1 * w0 + h0 * n1 + h1 * n0;
+  return (uint32_t)r | ((uint64_t)hi << 32);
+}
+
+// x mod q up to multiples of q, in [0, 2q + 2^32), for any x < 2^64 and
+// q > 2^32, with inv64 = floor(2^64 / q): the quotient estimate
+// floor(floor(x / 2^32) inv64 / 2^32) is at most x / q and falls short of it by
+// less than 2 + 2^32 / q.
+__host__ __device__ __forceinline__ uint64_t reduce64(uint64_t x, uint64_t q, uint32_t inv64) {
+  const uint32_t e = (uint32_t)(((x >> 32) * inv64) >> 32);
+  const uint64_t nq = 0 - q;
+  const uint64_t r = (uint64_t)e * (uint32_t)nq + x;
+  return (uint32_t)r | ((uint64_t)((uint32_t)(r >> 32) + e * (uint32_t)(nq >> 32)) << 32);
+}
+
 // x mod q for a sum x of at most 4 products of residues (x < 4 q^2, q < 2^61):
 // with s = bits(q) - 1, x / 2^s < 2^64 and mu = floor(2^(64+s) / q) < 2^64, and
 // qhat = (x >> s) mu / 2^64 falls short of x / q by less than 1 (the shift)
@@ -149,13 +174,13 @@ __host__ __device__ __forceinline__ double fp_mulmod(double x, double w, double 
   return fma(x, w, -h) - l;
 }
 
-// x * y mod q for two data operands (no precomputed quotient), q < 2^46,
-// |x| <= 4 q, |y| <= q: h = fl(x y) and l = x y - h (exact, |l| <= ulp(h)/2
-// <= 2^-53 4 q^2 < 2^-5 q) are the two-product; h/q < 4 q < 2^48, so
-// t = rint(h fl(1/q)) is within 1/2 + 2^-4 of h/q and h - t q is an integer
-// of magnitude below (1/2 + 2^-4) q: the FMA that forms it is exact; the
-// result h - t q + l is congruent to x y and below 0.6 q in magnitude, exact
-// as well.
+// x * y mod q without a precomputed quotient, q < 2^46, |x| <= 16 q, |y| <= q:
+// h = fl(x y) and l = x y - h (exact, |l| <= ulp(h)/2 <= 2^42) are the
+// two-product; |x y / q| < 2^50 and h fl(1/q) is within three roundings of it,
+// so t = rint(h fl(1/q)) is within 1/2 + 3/8 of x y / q; h - t q is an integer
+// below 2^53 in magnitude, so the FMA that forms it is exact, and so is the
+// result h - t q + l, congruent to x y and at most 7/8 q in magnitude (for
+// |x| <= 4 q at most 0.6 q).
 __host__ __device__ __forceinline__ double fp_mulmod_var(double x, double y, double q, double qinv) {
   const double h = x * y;
   const double l = fma(x, y, -h);

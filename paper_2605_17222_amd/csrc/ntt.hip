@@ -8,9 +8,9 @@
 // (a0 +- a1 tf; (a0 + a1), (a0 - a1) tf) are exactly these, with the halving
 // collected into N^-1.
 //
-// A limb of N = N1 N2 words is transformed in two passes of log2 N1 and
-// log2 N2 stages (at N = 2^16 a limb is 512 KiB, larger than one workgroup's
-// LDS):
+// N <= 2^13: one kernel (ntt_full below).  A larger limb of N = N1 N2 words is
+// transformed in two passes of log2 N1 and log2 N2 stages (at N = 2^16 a limb
+// is 512 KiB, larger than one workgroup's LDS):
 //   column pass: the first log2 N1 stages act on the N2 columns (stride N2)
 //                independently;
 //   row pass:    the last log2 N2 stages act on the N1 rows (contiguous)
@@ -20,8 +20,13 @@
 // in registers again.
 //
 // Two arithmetic paths, chosen per limb (uniform over a workgroup):
-//  * integer (q >= 2^46): Harvey's lazy butterflies ([0, 4q) forward,
-//    [0, 2q) inverse) with Shoup twiddle products;
+//  * integer (q >= 2^46): lazy butterflies with Shoup twiddle products whose
+//    quotient may be one short (mulhi64_under), so a product is in [0, 3q);
+//    values grow within 64 bits and are reduced as seldom as the prime's size
+//    allows (see Lazy below): about 16 instructions a butterfly against 29 with
+//    an exact quotient and a conditional subtraction (32 plaintexts of 44
+//    54-bit limbs at N = 2^16: column pass 401 -> 304 us, row pass 476 -> 397,
+//    with its twiddles from L2);
 //  * FP64 (q < 2^46): residues are doubles holding exact integers, the
 //    twiddle product is the exact FMA two-product remainder of modarith.hpp,
 //    values are re-centred every 4 stages.  Between the two passes such a limb
@@ -44,8 +49,124 @@ namespace {
 
 __device__ __forceinline__ int lds_pad(int i) { return i + (i >> 4); }
 
+// A read-only table: read by scalar loads where the index is uniform, else by global (not flat) ones.
+typedef const __attribute__((address_space(4))) uint64_t* TableWords;
+
+// How far an integer-path prime lets values grow within 64 bits:
+//   kFree (q < 2^58, 64 q): a forward transform of 16 stages from [0, q) ends
+//     below q + 16 * 3q = 49 q; an inverse round of 4 stages from [0, 3q) below
+//     48 q, its sums reduced once a round;
+//   kRounds (q < 2^60, 16 q): forward, all values reduced to [0, 2q + 2^32) at
+//     each round of at most 4 stages (+ 12 q); inverse, sums reduced after two
+//     stages (12 q) and at the end of a round;
+//   kStages (q < 2^61, 8 q): one operand of each butterfly reduced (5 q + 2^32
+//     forward, 6 q inverse).
+enum Lazy { kFree, kRounds, kStages };
+__device__ __forceinline__ Lazy lazy_of(uint64_t q) { return q < (1ull << 58) ? kFree : (q < (1ull << 60) ? kRounds : kStages); }
+
 __device__ __forceinline__ double as_d(uint64_t u) { return __longlong_as_double((long long)u); }
 __device__ __forceinline__ uint64_t as_u(double d) { return (uint64_t)__double_as_longlong(d); }
+
+// The range of a launch that limb number `limb` falls in (a branch-free binary
+// search: a walk over up to 32 ranges costs a chain of dependent loads, which a
+// short workgroup notices: 21.6 -> 17.4 us for 320 limbs of 2^13).
+__device__ __forceinline__ int find_range(const NttArgs& a, int limb) {
+  static_assert((kMaxRanges & (kMaxRanges - 1)) == 0, "binary search");
+  int ri = 0;
+#pragma unroll
+  for (int step = kMaxRanges / 2; step > 0; step /= 2) ri += limb >= a.start[ri + step] ? step : 0;
+  return ri;
+}
+
+// The arithmetic of one direction and path on a thread's NW words (integer
+// residues, or double bits on the FP path).
+template <bool FP, bool FWD, int NW = 16>
+struct Butterflies {
+  const PrimeDev& pr;
+  const uint64_t q, q3;
+  const Lazy lazy;
+  const uint32_t inv64;  // integer path: floor(2^64 / q), below 2^18
+  const double qd, qi;
+  uint64_t cy = 0;  // inverse, integer path: a multiple of q that no value exceeds
+  uint64_t v[NW];
+
+  __device__ __forceinline__ explicit Butterflies(const PrimeDev& r)
+      : pr(r), q(r.q), q3(3 * r.q), lazy(lazy_of(r.q)), inv64((uint32_t)r.r_hi), qd(r.qd), qi(r.qinv_d) {}
+
+  // One butterfly between words u and u + d; the twiddle is (w, wp): the value
+  // and its Shoup word, or, on the FP path, w as double bits alone (a product
+  // that forms its quotient from x w costs as many operations as one that
+  // takes w/q, and half the twiddle words).
+  __device__ __forceinline__ void bfly(int u, int d, uint64_t tw_w, uint64_t tw_p) {
+    if (FP) {
+      const double w = as_d(tw_w);
+      const double X = as_d(v[u]), Y = as_d(v[u + d]);
+      if (FWD) {
+        const double r = fp_mulmod_var(Y, w, qd, qi);
+        v[u] = as_u(X + r);
+        v[u + d] = as_u(X - r);
+      } else {
+        v[u] = as_u(X + Y);
+        v[u + d] = as_u(fp_mulmod_var(X - Y, w, qd, qi));
+      }
+    } else if (FWD) {
+      uint64_t X = v[u];
+      if (lazy == kStages) X = reduce64(X, q, inv64);
+      // X + t and X - t + 3q, t = v w - qhat q
+      const uint64_t sum = shoup_add(X, v[u + d], tw_w, tw_p, q);
+      v[u] = sum;
+      v[u + d] = 2 * X + q3 - sum;
+    } else {
+      const uint64_t X = v[u], Y = v[u + d];
+      v[u] = X + Y;
+      v[u + d] = shoup_add(0, X - Y + cy, tw_w, tw_p, q);
+    }
+  }
+  // Inverse, integer path, stage k of a round: cy before it; after it (its
+  // butterflies d apart), the sums that have to be reduced.
+  __device__ __forceinline__ void stage_begin(int k) {
+    if (!FP && !FWD) cy = q3 << (lazy == kFree ? k : (lazy == kRounds ? k & 1 : 0));
+  }
+  __device__ __forceinline__ void stage_end(int k, bool last, int d) {
+    if (FP || FWD) return;
+    if (last || lazy == kStages || (lazy == kRounds && (k & 1))) {
+#pragma unroll
+      for (int u = 0; u < NW; ++u)
+        if (!(u & d)) v[u] = reduce64(v[u], q, inv64);
+    }
+  }
+  // Between rounds of at most 4 stages.
+  __device__ __forceinline__ void recentre() {
+    if (FP) {
+#pragma unroll
+      for (int u = 0; u < NW; ++u) v[u] = as_u(fp_reduce(as_d(v[u]), qd, qi));
+    } else if (FWD && lazy == kRounds) {
+#pragma unroll
+      for (int u = 0; u < NW; ++u) v[u] = reduce64(v[u], q, inv64);
+    }
+  }
+  // Canonical residues arrive as integers; the FP path converts them.
+  __device__ __forceinline__ void convert_in() {
+    if (FP) {
+#pragma unroll
+      for (int u = 0; u < NW; ++u) v[u] = as_u(u64_to_d(v[u]));
+    }
+  }
+  // A signed coefficient |m| < 2^62 -> residue: |m / q| < 2^33, so the
+  // estimated quotient is within one of the floor and r lands in [-q, 2q).
+  __device__ __forceinline__ uint64_t residue(int64_t m) const {
+    const int64_t qs = (int64_t)q;
+    int64_t r = m - (int64_t)floor((double)m * qi) * qs;
+    r = r < 0 ? r + qs : r;
+    return (uint64_t)(r >= qs ? r - qs : r);
+  }
+  // Final values -> canonical residues: forward, and inverse with the factor
+  // N^-1.
+  __device__ __forceinline__ uint64_t canon(uint64_t x) const {
+    if (FWD) return FP ? fp_canon(as_d(x), qd, qi) : csub(csub(reduce64(x, q, inv64), q), q);
+    return FP ? fp_canon(fp_mulmod(as_d(x), pr.ninv_d, pr.ninv_q, qd), qd, qi) : shoup(x, pr.ninv, pr.ninv_sh, q);
+  }
+};
 
 // SIN (forward column pass only): the input is the range's shared signed
 // coefficients (LimbRange::signed_in).
@@ -55,10 +176,10 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
   constexpr int P = 1 << PLOG;
   constexpr int T = P / 16;           // threads per sub-transform
   constexpr int RS = P + P / 16 + 1;  // LDS row stride (padded)
-  const uint64_t q = pr.q, q2 = 2 * q;
-  const double qd = pr.qd, qi = pr.qinv_d;
+  Butterflies<FP, FWD> F(pr);
+  uint64_t(&v)[16] = F.v;
   const int n = 1 << log_n;
-  const uint64_t* __restrict__ tw = pr.tw + (FWD ? 0 : 2 * (size_t)n);
+  const TableWords tw = (TableWords)(pr.tw + (FWD ? 0 : 2 * (size_t)n));
   const bool first = (COL == FWD);  // first pass of the transform
   const uint64_t* __restrict__ src = (first ? R.in : R.out) + (SIN ? 0 : (size_t)limb * n);
   uint64_t* __restrict__ dst = R.out + (size_t)limb * n;
@@ -77,7 +198,6 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
   const uint32_t base = COL ? 1u : (uint32_t)((n >> PLOG) + sub);
   uint64_t* L = lds + g * RS;
 
-  uint64_t v[16];  // integer residues, or double bits on the FP path
   auto addr = [&](int x) -> size_t { return COL ? (size_t)x * ncols + sub : (size_t)sub * P + x; };
 
   // FP row pass: the factor tables of this direction, G (P doubles, shared
@@ -95,52 +215,20 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
       __syncthreads();
     }
   };
-  // Twiddle of stage s, group y (index base 2^s + y): the value and its
-  // companion (Shoup word, or w/q on the FP path), as raw 64-bit words.
+  // Twiddle of stage s, group y (index base 2^s + y): the value and, on the
+  // integer path, its Shoup word, as raw 64-bit words.
   auto twid = [&](int s, uint32_t y, uint64_t& w, uint64_t& wp) {
     if (FP && !COL) {
-      // |w| <= 0.75 q; wq = w/q to within 2 ulp, which keeps the products
-      // that use it within the bounds of fp_mulmod.
-      const double wv = fp_mulmod(tg[(1u << s) + y], tr[2 * s], tr[2 * s + 1], qd);
-      w = as_u(wv);
-      wp = as_u(wv * qi);
+      // |w| <= 0.75 q
+      w = as_u(fp_mulmod(tg[(1u << s) + y], tr[2 * s], tr[2 * s + 1], F.qd));
+      wp = 0;
     } else {
       const uint32_t ti = (base << s) + y;
       w = tw[ti];
-      wp = tw[n + ti];
+      wp = FP ? 0 : tw[n + ti];
     }
   };
 
-  // One butterfly between registers u and u + d with twiddle (tw_w, tw_p).
-  auto bfly = [&](int u, int d, uint64_t tw_w, uint64_t tw_p) {
-    if (FP) {
-      const double w = as_d(tw_w), wq = as_d(tw_p);
-      const double X = as_d(v[u]), Y = as_d(v[u + d]);
-      if (FWD) {
-        const double r = fp_mulmod(Y, w, wq, qd);
-        v[u] = as_u(X + r);
-        v[u + d] = as_u(X - r);
-      } else {
-        v[u] = as_u(X + Y);
-        v[u + d] = as_u(fp_mulmod(X - Y, w, wq, qd));
-      }
-    } else {
-      const uint64_t w = tw_w, wp = tw_p;
-      if (FWD) {
-        uint64_t X = v[u];
-        X = X >= q2 ? X - q2 : X;
-        const uint64_t t = shoup_lazy(v[u + d], w, wp, q);
-        v[u] = X + t;
-        v[u + d] = X - t + q2;
-      } else {
-        const uint64_t X = v[u], Y = v[u + d];
-        uint64_t sm = X + Y;
-        sm = sm >= q2 ? sm - q2 : sm;
-        v[u] = sm;
-        v[u + d] = shoup_lazy(X - Y + q2, w, wp, q);
-      }
-    }
-  };
   // Stages 0..3 in layout "x = j + T u": group y = u >> (4 - s), 2^s groups.
   auto round1 = [&]() {
 #pragma unroll
@@ -150,9 +238,11 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
       uint64_t W[8], WP[8];
 #pragma unroll
       for (int y = 0; y < (1 << s); ++y) twid(s, (uint32_t)y, W[y], WP[y]);
+      F.stage_begin(k);
 #pragma unroll
       for (int u = 0; u < 16; ++u)
-        if (!(u & d)) bfly(u, d, W[u >> (4 - s)], WP[u >> (4 - s)]);
+        if (!(u & d)) F.bfly(u, d, W[u >> (4 - s)], WP[u >> (4 - s)]);
+      F.stage_end(k, k == 3, d);
     }
   };
   // Stages 4..PLOG-1 in layout "x = 16 j + u": group (16 j + u) >> sh with
@@ -167,15 +257,11 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
       uint64_t W[8], WP[8];
 #pragma unroll
       for (int c = 0; c < (16 >> sh); ++c) twid(s, y0 + (uint32_t)c, W[c], WP[c]);
+      F.stage_begin(k - 4);
 #pragma unroll
       for (int u = 0; u < 16; ++u)
-        if (!(u & d)) bfly(u, d, W[u >> sh], WP[u >> sh]);
-    }
-  };
-  auto recentre = [&]() {
-    if (FP) {
-#pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = as_u(fp_reduce(as_d(v[u]), qd, qi));
+        if (!(u & d)) F.bfly(u, d, W[u >> sh], WP[u >> sh]);
+      F.stage_end(k - 4, k == PLOG - 1, d);
     }
   };
   auto to_lds = [&](bool layout1) {
@@ -186,42 +272,22 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
 #pragma unroll
     for (int u = 0; u < 16; ++u) v[u] = L[lds_pad(layout1 ? (j + T * u) : (16 * j + u))];
   };
-  // Canonical residues arrive as integers; the FP path converts them.
-  auto convert_in = [&]() {
-    if (FP) {
-#pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = as_u(u64_to_d(v[u]));
-    }
-  };
-  // Final values -> canonical residues.
-  auto canon = [&](uint64_t x) -> uint64_t {
-    if (FP) return fp_canon(as_d(x), qd, qi);
-    x = x >= q2 ? x - q2 : x;
-    return csub(x, q);
-  };
-
   if (FWD) {
     if constexpr (SIN) {
-      // signed coefficients -> residues: |m / q| < 2^33, so the estimated
-      // quotient is within one of the floor and r lands in [-q, 2q)
       const int64_t* __restrict__ sc = reinterpret_cast<const int64_t*>(src);
-      const int64_t qs = (int64_t)q;
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int64_t m = sc[addr(j + T * u)];
-        int64_t r = m - (int64_t)floor((double)m * qi) * qs;
-        r = r < 0 ? r + qs : r;
-        r = r >= qs ? r - qs : r;
-        v[u] = (uint64_t)r;
-      }
+      for (int u = 0; u < 16; ++u) v[u] = F.residue(sc[addr(j + T * u)]);
     } else {
 #pragma unroll
       for (int u = 0; u < 16; ++u) v[u] = __builtin_nontemporal_load(src + addr(j + T * u));
     }
     if (!COL) stage_tw();
-    if (first) convert_in();
+    if (first)
+      F.convert_in();
+    else if (!FP)
+      F.recentre();
     round1();
-    recentre();
+    F.recentre();
     to_lds(true);
     __syncthreads();
     from_lds(false);
@@ -244,8 +310,8 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         const int x = j + T * u;
-        uint64_t y = canon(v[u]);
-        if (epi == EPI_SUBMUL) y = shoup(__builtin_nontemporal_load(aux + addr(x)) - y + q, c, cs, q);
+        uint64_t y = F.canon(v[u]);
+        if (epi == EPI_SUBMUL) y = shoup(__builtin_nontemporal_load(aux + addr(x)) - y + F.q, c, cs, F.q);
         dst[addr(x)] = y;
       }
     }
@@ -267,9 +333,9 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
       from_lds(false);
       __syncthreads();
     }
-    if (first) convert_in();
+    if (first) F.convert_in();
     round2();
-    recentre();
+    F.recentre();
     to_lds(false);
     __syncthreads();
     from_lds(true);
@@ -277,16 +343,9 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
     if (!first) {
       // last pass: times N^-1, canonical
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        uint64_t y;
-        if (FP)
-          y = fp_canon(fp_mulmod(as_d(v[u]), pr.ninv_d, pr.ninv_q, qd), qd, qi);
-        else
-          y = shoup(v[u], pr.ninv, pr.ninv_sh, q);
-        dst[addr(j + T * u)] = y;
-      }
+      for (int u = 0; u < 16; ++u) dst[addr(j + T * u)] = F.canon(v[u]);
     } else {
-      recentre();
+      F.recentre();
 #pragma unroll
       for (int u = 0; u < 16; ++u) dst[addr(j + T * u)] = v[u];
     }
@@ -294,7 +353,7 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
 }
 
 template <int PLOG, int G, bool COL, bool FWD, bool SIN>
-__global__ void __launch_bounds__(G*(1 << PLOG) / 16)
+__global__ void __launch_bounds__(G*(1 << PLOG) / 16) __attribute__((amdgpu_waves_per_eu(COL ? 1 : 4)))
     ntt_pass(NttArgs args, const PrimeDev* __restrict__ primes, int log_n, int epi) {
   constexpr int P = 1 << PLOG;
   constexpr int RS = P + P / 16 + 1;
@@ -303,9 +362,12 @@ __global__ void __launch_bounds__(G*(1 << PLOG) / 16)
   // Which limb (uniform over the workgroup).
   int limb = blockIdx.y;
   int ri = 0;
-  while (ri < args.nr - 1 && limb >= args.r[ri].count) {
-    limb -= args.r[ri].count;
-    ++ri;
+  if (args.interleave) {
+    ri = limb % args.nr;
+    limb /= args.nr;
+  } else {
+    ri = find_range(args, limb);
+    limb -= args.start[ri];
   }
   const LimbRange& R = args.r[ri];
   const PrimeDev& pr = primes[R.prime0 + limb];
@@ -315,13 +377,172 @@ __global__ void __launch_bounds__(G*(1 << PLOG) / 16)
     ntt_body<PLOG, G, COL, FWD, false, SIN>(R, limb, pr, log_n, epi, lds, tws);
 }
 
+// ---- N <= 2^13: a whole transform in one workgroup ---------------------------
+// A limb of at most 2^13 words (64 KiB, 68 KiB padded) leaves room for two
+// workgroups in a CU's LDS, so all its stages run in one kernel of N / 16
+// threads (N / 8 for small launches): rounds of at most 4 stages in registers
+// with an LDS exchange between them, half the launches and half the memory
+// traffic of two passes: (2,2,4) at N = 2^12 168 -> 117 us, the encoded
+// plaintexts' forward passes of the dense LT at N = 2^13 4.84 -> 3.76 ms.  Bound
+// by latency (few waves per SIMD) and VALU issue.  (At N = 2^14 a workgroup
+// would take a whole CU, and a launch of a few dozen limbs a few dozen CUs:
+// measured slower, 208 -> 276 us of forward passes at (4,4,8), level 22.)
+// Stage s pairs words 2^(log N-1-s) apart with twiddle 2^s + (x >> (log N - s)),
+// read from the full table (small enough at these N to stay in L2).  Round r's
+// registers u are LW consecutive bits of x from bit fb up; its k stages use k
+// of them.
+template <int LOGN, int LW>  // 2^LW words per thread
+struct FullRounds {
+  static constexpr int kRoundsN = (LOGN + LW - 1) / LW;
+  // as even as they divide, longer rounds first
+  static constexpr int k(int r) { return LOGN / kRoundsN + (r < LOGN % kRoundsN ? 1 : 0); }
+  static constexpr int s0(int r) { return r == 0 ? 0 : s0(r - 1) + k(r - 1); }
+  // first of the LW bits of x that round r's registers stand for (the
+  // last round's spare bit, if any, is above its stages)
+  static constexpr int fb(int r) { return LOGN - s0(r) - LW > 0 ? LOGN - s0(r) - LW : 0; }
+  static_assert(k(0) <= LW && s0(kRoundsN - 1) + k(kRoundsN - 1) == LOGN, "all stages");
+};
+template <int LW>
+__device__ __forceinline__ uint32_t full_pad(uint32_t i) { return i + (i >> LW); }
+
+// Word x of register u of thread t in the layout with field base FB.
+template <int LW, int FB>
+__device__ __forceinline__ uint32_t full_at(uint32_t t, int u) {
+  return ((t >> FB) << (FB + LW)) | ((uint32_t)u << FB) | (t & ((1u << FB) - 1));
+}
+
+template <int LW, int FROM, int TO>
+__device__ __forceinline__ void full_layout(uint64_t (&v)[(1 << LW)], uint32_t t, uint64_t* lds) {
+  if constexpr (FROM != TO) {
+#pragma unroll
+    for (int u = 0; u < (1 << LW); ++u) lds[full_pad<LW>(full_at<LW, FROM>(t, u))] = v[u];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < (1 << LW); ++u) v[u] = lds[full_pad<LW>(full_at<LW, TO>(t, u))];
+    __syncthreads();
+  }
+}
+
+// The twiddles of a stage: groups GB apart in the butterfly order, at most
+// 2^(LW-1) per thread.
+template <int LW>
+struct FullTwiddles {
+  uint64_t w[(1 << LW) / 2], wp[(1 << LW) / 2];
+};
+template <int LOGN, int LW, bool FWD, bool FP, int I, int J>
+__device__ __forceinline__ void full_twiddles(FullTwiddles<LW>& T, TableWords tw, uint32_t t) {
+  typedef FullRounds<LOGN, LW> FR;
+  if constexpr (I < FR::kRoundsN) {
+    constexpr int r = FWD ? I : FR::kRoundsN - 1 - I;
+    constexpr int fb = FR::fb(r), s = FWD ? FR::s0(r) + J : FR::s0(r) + FR::k(r) - 1 - J, bp = LOGN - 1 - s - fb;
+    const uint32_t y0 = (1u << s) + ((t >> fb) << (LW - 1 - bp));
+#pragma unroll
+    for (int c = 0; c < ((1 << LW) / 2 >> bp); ++c) {
+      T.w[c] = tw[y0 + c];
+      if (!FP) T.wp[c] = tw[(1 << LOGN) + y0 + c];
+    }
+  }
+}
+
+// Stage J of round I and all that follow, v arriving in the layout HAVE and
+// leaving in that of the global memory accesses.  T holds the stage's twiddles;
+// the next stage's are loaded before this one's butterflies.
+template <int LOGN, int LW, bool FWD, bool FP, int I, int J, int HAVE>
+__device__ __forceinline__ void full_stages(Butterflies<FP, FWD, (1 << LW)>& F, const FullTwiddles<LW>& T, TableWords tw, uint32_t t,
+                                            uint64_t* lds) {
+  typedef FullRounds<LOGN, LW> FR;
+  if constexpr (I == FR::kRoundsN) {
+    full_layout<LW, HAVE, LOGN - LW>(F.v, t, lds);
+  } else {
+    constexpr int r = FWD ? I : FR::kRoundsN - 1 - I;
+    constexpr int fb = FR::fb(r), k = FR::k(r), s = FWD ? FR::s0(r) + J : FR::s0(r) + k - 1 - J;
+    constexpr int bp = LOGN - 1 - s - fb, d = 1 << bp;  // the stage's bit among the registers
+    if constexpr (J == 0) {
+      full_layout<LW, HAVE, fb>(F.v, t, lds);
+      if (I > 0) F.recentre();
+    }
+    constexpr bool last = J == k - 1;
+    constexpr int I1 = last ? I + 1 : I, J1 = last ? 0 : J + 1;
+    FullTwiddles<LW> T1;
+    full_twiddles<LOGN, LW, FWD, FP, I1, J1>(T1, tw, t);
+    __builtin_amdgcn_sched_barrier(0);
+    F.stage_begin(J);
+#pragma unroll
+    for (int u = 0; u < (1 << LW); ++u)
+      if (!(u & d)) F.bfly(u, d, T.w[u >> (bp + 1)], T.wp[u >> (bp + 1)]);
+    F.stage_end(J, last, d);
+    full_stages<LOGN, LW, FWD, FP, I1, J1, fb>(F, T1, tw, t, lds);
+  }
+}
+
+template <int LOGN, int LW, bool FWD, bool FP, bool SIN>
+__device__ __forceinline__ void ntt_full_body(const LimbRange& R, int limb, const PrimeDev& pr, int epi,
+                                              uint64_t* lds) {
+  constexpr int n = 1 << LOGN, kTop = LOGN - LW;  // global memory is accessed as x = u 2^kTop + t
+  Butterflies<FP, FWD, (1 << LW)> F(pr);
+  uint64_t(&v)[(1 << LW)] = F.v;
+  const uint64_t* __restrict__ src = R.in + (SIN ? 0 : (size_t)limb * n);
+  uint64_t* __restrict__ dst = R.out + (size_t)limb * n;
+  const uint32_t t = threadIdx.x;
+  auto at = [&](int u) -> uint32_t { return full_at<LW, kTop>(t, u); };
+  if constexpr (SIN) {
+    const int64_t* __restrict__ sc = reinterpret_cast<const int64_t*>(src);
+#pragma unroll
+    for (int u = 0; u < (1 << LW); ++u) v[u] = F.residue(sc[at(u)]);
+  } else {
+#pragma unroll
+    for (int u = 0; u < (1 << LW); ++u) v[u] = __builtin_nontemporal_load(src + at(u));
+  }
+  if (!FWD && R.copy) {
+    uint64_t* __restrict__ cp = R.copy + (size_t)limb * n;
+#pragma unroll
+    for (int u = 0; u < (1 << LW); ++u) cp[at(u)] = v[u];
+  }
+  const TableWords tw = (TableWords)(pr.tw + (FWD ? 0 : 2 * (size_t)n));
+  FullTwiddles<LW> T;
+  full_twiddles<LOGN, LW, FWD, FP, 0, 0>(T, tw, t);
+  F.convert_in();
+  full_stages<LOGN, LW, FWD, FP, 0, 0, kTop>(F, T, tw, t, lds);
+  if (FWD && epi == EPI_SUBMUL) {
+    const uint64_t* aux = R.aux + (size_t)limb * n;
+    const uint64_t c = R.sinv[limb], cs = R.sinv_sh[limb];
+#pragma unroll
+    for (int u = 0; u < (1 << LW); ++u)
+      dst[at(u)] = shoup(__builtin_nontemporal_load(aux + at(u)) - F.canon(v[u]) + F.q, c, cs, F.q);
+  } else {
+#pragma unroll
+    for (int u = 0; u < (1 << LW); ++u) dst[at(u)] = F.canon(v[u]);
+  }
+}
+
+template <int LOGN, int LW, bool FWD, bool SIN>
+__global__ void __launch_bounds__(1 << (LOGN - LW)) __attribute__((amdgpu_waves_per_eu(4)))
+    ntt_full(NttArgs args, const PrimeDev* __restrict__ primes, int epi) {
+  __shared__ uint64_t lds[(1 << LOGN) + (1 << LOGN) / (1 << LW)];
+  int limb = blockIdx.x;
+  const int ri = find_range(args, limb);
+  limb -= args.start[ri];
+  const LimbRange& R = args.r[ri];
+  const PrimeDev& pr = primes[R.prime0 + limb];
+  if (pr.fp)
+    ntt_full_body<LOGN, LW, FWD, true, SIN>(R, limb, pr, epi, lds);
+  else
+    ntt_full_body<LOGN, LW, FWD, false, SIN>(R, limb, pr, epi, lds);
+}
+
 // Sub-transforms per workgroup: 4096 / P (16 at N = 2^16: 256 threads,
 // 128-byte column segments).  A quarter of that for launches over a few
 // limbs (4x the workgroups) was measured slower: the inverse column pass
 // over 9-10 limbs 0.106 -> 0.147 ms per (4,4,4) LT, its 32-byte column
 // segments costing more than the extra workgroups gain.
+// Row passes of ranges over the same integer-path primes (the plaintexts of an
+// encoding launch) are taken prime by prime, not range by range: such a pass
+// reads twice as many twiddle words as data words, and this way they come from
+// L2 after the first range (44 limbs of 54 bits x 32 plaintexts at N = 2^16:
+// 369 -> 325 us; FP64-path limbs read small tables and are better off range by
+// range, as are column passes, whose input all limbs of a range share).
 template <int PLOG, bool COL, bool FWD>
-hipError_t launch_pass(const ckks_params* P, const NttArgs& a, int total, int epi, hipStream_t s) {
+hipError_t launch_pass(const ckks_params* P, NttArgs& a, int total, int epi, hipStream_t s) {
   constexpr int Pn = 1 << PLOG;
   constexpr int G = 4096 / Pn;
   const int n = P->n;
@@ -333,11 +554,12 @@ hipError_t launch_pass(const ckks_params* P, const NttArgs& a, int total, int ep
   double words = (double)total * n * (epi == EPI_SUBMUL ? 3 : 2);
   if (!FWD && !COL)
     for (int i = 0; i < a.nr; ++i) words += a.r[i].copy ? (double)a.r[i].count * n : 0;
-  // signed input: every range of the launch, forward transforms only
   const bool sin = a.r[0].signed_in != 0;
-  for (int i = 1; i < a.nr; ++i)
-    if ((a.r[i].signed_in != 0) != sin) return hipErrorInvalidValue;
-  if (sin && !FWD) return hipErrorInvalidValue;
+  a.interleave = !COL && a.nr > 1;
+  for (int i = 0; i < a.nr; ++i)
+    if (a.r[i].prime0 != a.r[0].prime0 || a.r[i].count != a.r[0].count) a.interleave = 0;
+  for (int l = 0; l < a.r[0].count; ++l)
+    if (P->primes[a.r[0].prime0 + l] < kFpPrimeLimit) a.interleave = 0;
   ProfScope prof(id, s, words * 8);
   if constexpr (COL && FWD) {
     if (sin) {
@@ -352,7 +574,7 @@ hipError_t launch_pass(const ckks_params* P, const NttArgs& a, int total, int ep
 }
 
 template <int PA, int PB>
-hipError_t launch_both(const ckks_params* P, bool forward, const NttArgs& a, int total, int epi, hipStream_t s) {
+hipError_t launch_both(const ckks_params* P, bool forward, NttArgs& a, int total, int epi, hipStream_t s) {
   hipError_t e;
   if (forward) {
     e = launch_pass<PA, true, true>(P, a, total, EPI_NONE, s);
@@ -364,14 +586,49 @@ hipError_t launch_both(const ckks_params* P, bool forward, const NttArgs& a, int
   return launch_pass<PA, true, false>(P, a, total, EPI_NONE, s);
 }
 
+// The whole transform in one launch.  Timed as the column pass of its
+// direction.
+template <int LOGN, int LW>
+hipError_t launch_full(const ckks_params* P, bool forward, const NttArgs& a, int total, int epi, hipStream_t s) {
+  double words = (double)total * P->n * (epi == EPI_SUBMUL ? 3 : 2);
+  for (int i = 0; i < a.nr; ++i) words += a.r[i].copy ? (double)a.r[i].count * P->n : 0;
+  ProfScope prof(forward ? CKKS_KERNEL_NTT_FWD_COL : CKKS_KERNEL_NTT_INV_COL, s, words * 8);
+  const dim3 grid(total), block(1 << (LOGN - LW));
+  if (!forward)
+    hipLaunchKernelGGL((ntt_full<LOGN, LW, false, false>), grid, block, 0, s, a, P->d_primes, epi);
+  else if (a.r[0].signed_in)
+    hipLaunchKernelGGL((ntt_full<LOGN, LW, true, true>), grid, block, 0, s, a, P->d_primes, epi);
+  else
+    hipLaunchKernelGGL((ntt_full<LOGN, LW, true, false>), grid, block, 0, s, a, P->d_primes, epi);
+  return hipGetLastError();
+}
+
 }  // namespace
 
-hipError_t launch_ntt(const ckks_params* P, bool forward, const NttArgs& a, int total_limbs, int epi,
+hipError_t launch_ntt(const ckks_params* P, bool forward, const NttArgs& args, int total_limbs, int epi,
                       hipStream_t s) {
   if (total_limbs <= 0) return hipSuccess;
+  NttArgs a = args;
+  // signed input: every range of the launch or none, forward transforms only
+  for (int i = 0; i < a.nr; ++i)
+    if ((a.r[i].signed_in != 0) != (a.r[0].signed_in != 0) || (a.r[i].signed_in && !forward))
+      return hipErrorInvalidValue;
+  int at = 0;
+  for (int i = 0; i < kMaxRanges; ++i) {
+    a.start[i] = i < a.nr ? at : INT32_MAX;
+    at += i < a.nr ? a.r[i].count : 0;
+  }
+  if (at != total_limbs) return hipErrorInvalidValue;
   switch (P->log_n) {
-    case 12: return launch_both<6, 6>(P, forward, a, total_limbs, epi, s);
-    case 13: return launch_both<7, 6>(P, forward, a, total_limbs, epi, s);
+    // Words per thread of the one-kernel transforms: a launch of at most a limb
+    // per CU is bound by one workgroup's latency, so its limbs are spread over
+    // more waves (8 words a thread against 16: 16 -> 12 us a transform of 2^12,
+    // 20 -> 18 us of 2^13); larger ones run faster with fewer exchanges (1280
+    // limbs of 2^13: 33 -> 29 us per 320).
+    case 12: return launch_full<12, 3>(P, forward, a, total_limbs, epi, s);
+    case 13:
+      return total_limbs <= 256 ? launch_full<13, 3>(P, forward, a, total_limbs, epi, s)
+                                : launch_full<13, 4>(P, forward, a, total_limbs, epi, s);
     case 14: return launch_both<7, 7>(P, forward, a, total_limbs, epi, s);
     case 15: return launch_both<8, 7>(P, forward, a, total_limbs, epi, s);
     case 16: return launch_both<8, 8>(P, forward, a, total_limbs, epi, s);

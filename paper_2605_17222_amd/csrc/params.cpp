@@ -201,7 +201,7 @@ int params_create(const ckks_params_desc* d, ckks_params** out) {
       b = mm(b, psi_inv, q);
     }
     const bool fp = q < kFpPrimeLimit;
-    if (fp) {
+    if (fp && !ntt_one_kernel(P->log_n)) {  // the two-pass transform's row factors
       std::vector<uint64_t> full_f(n), full_i(n);
       for (int k = 0; k < n; ++k) {
         const uint32_t r = brev(k, P->log_n);
