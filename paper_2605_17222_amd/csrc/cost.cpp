@@ -155,8 +155,10 @@ int ckks_lt_predict(int log_n, int level, int alpha, int algo, int n1, int n2, i
     conv += (double)gs * (K - gs);
   }
   const double bconv_products = (c.decompose * conv + c.moddown * alpha * Lq) * N;
-  // Words moved per coefficient position by the HBM-bound kernels as this
-  // library schedules one LT: a key (2 beta K words at this level) is read
+  // Words moved per coefficient position by the HBM-bound kernels in the
+  // schedule that the default rates were fitted to (the library now also fuses
+  // 5 to 8 accumulators with more terms, and runs up to 64 terms a launch; the
+  // model is kept with its rates, so that splits are chosen as before): a key (2 beta K words at this level) is read
   // once per launch for every digit set that uses it (up to 8 digit sets per
   // launch).  With at most 4 accumulators, or at most 8 and terms that fit
   // one launch, the middle key switch runs fused with the multiply-
