@@ -113,9 +113,11 @@ struct LimbRange {
 constexpr int kMaxRanges = 32;
 struct NttArgs {
   int nr = 0;
-  // Set by the launch: where each range starts in the sequence of limbs, or
-  // every range covers the same primes and they are taken prime by prime.
+  // Set by the launch: where each range starts in the sequence of limbs and the
+  // first step of a binary search over them, or that every range covers the same
+  // primes and they are taken prime by prime.
   int interleave = 0;
+  int search = 0;
   int start[kMaxRanges];
   LimbRange r[kMaxRanges];
 };
@@ -173,20 +175,21 @@ struct KsGatherArgs {
 
 // Lines 8-14 of Algorithm 2 in one pass (middle key switch fused with the
 // plaintext multiply-accumulate).  First nu unrotated terms, (a_m, b_m) read
-// at the output position; then nr rotated ones in groups of ni that share a
-// key (group g: key[g], gal[g]): at output position p the product <d, swk>
+// at the output position; then nr rotated ones in groups that share a key
+// (group g: key[g], gal[g]): at output position p the product <d, swk>
 // and the add a[m] are formed at auto_index(p, gal[g]), so the rotated
 // (a_m, b_m) exist only in registers.  Every pointer of a term is readable:
 // an absent plaintext's entry repeats a present one of the term and its meta
 // bit is clear.
 constexpr int kKsMacAlign = 2048;  // N must be a multiple: 256 threads per workgroup x 8 XCDs
 constexpr uint32_t kKsMacPscaled = 1u << 8;  // meta: a (and b) are Q-basis polynomials to be multiplied by P
+constexpr int kKsMacEnd = 16;                // meta of a group's first term, from this bit: one past its last term
 struct KsMacArgs {
-  int nu, nr, ni, nk, K, beta, kmax;
+  int nu, nr, groups, nk, K, beta, kmax;
   int accumulate;                    // add into the outputs
   int key_packed, f_packed;          // every key / every plaintext of the launch is packed (else none is)
   uint64_t pk_poly_bytes;            // bytes of one packed PQ polynomial
-  uint32_t meta[kMaxKsTerms];        // bit k: accumulator k has a plaintext; kKsMacPscaled
+  uint32_t meta[kMaxKsTerms];        // bit k: accumulator k has a plaintext; kKsMacPscaled; kKsMacEnd
   const uint64_t* a[kMaxKsTerms];    // the add (rotated) or a_m (unrotated)
   const uint64_t* db[kMaxKsTerms];   // rotated terms: digits [beta][K][N]; unrotated: b_m
   const uint64_t* key[kMaxKsKeys];   // [beta_max][2][kmax][N], or packed [beta_max][2] polynomials

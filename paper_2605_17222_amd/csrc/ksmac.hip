@@ -11,16 +11,20 @@ hipError_t launch_ksmac_nk(const ckks_params* P, const KsMacArgs& a, hipStream_t
 
 hipError_t launch_ksmac(const ckks_params* P, const KsMacArgs& a, hipStream_t s) {
   // Geometry, checked before anything runs: term and accumulator counts
-  // within the tables, rotated terms in whole groups with a key each, every
-  // operand present (the kernel reads them unconditionally).
+  // within the tables, groups that cover the rotated terms, each with a key,
+  // every operand present (the kernel reads them unconditionally).
   const int nm = a.nu + a.nr;
   if (a.nu < 0 || a.nr < 0 || nm < 1 || nm > kMaxKsTerms || a.nk < 1 || a.nk > kMaxMacK || nm * a.nk > kMaxKsPts ||
       a.K < 1 || a.K > a.kmax || a.beta < 1 || a.beta > kMaxBeta || P->n % kKsMacAlign ||
-      a.ni < 1 || (a.ni > 1 && a.ni % 2) || a.nr % a.ni || a.nr / a.ni > kMaxKsKeys ||
-      (a.ni != 1 && a.key_packed != a.f_packed))
+      a.groups < (a.nr > 0) || a.groups > a.nr || a.groups > kMaxKsKeys)
     return hipErrorInvalidValue;
+  for (int g = 0, m = a.nu; g < a.groups; ++g) {
+    const int end = (int)(a.meta[m] >> kKsMacEnd);
+    if (end <= m || end > nm || (g + 1 == a.groups) != (end == nm)) return hipErrorInvalidValue;
+    m = end;
+  }
   int nkeys = 0, ndig = 0, nadd = 0, nf = 0;
-  for (int g = 0; g < a.nr / a.ni; ++g) {
+  for (int g = 0; g < a.groups; ++g) {
     if (!a.key[g]) return hipErrorInvalidValue;
     nkeys += std::find(a.key, a.key + g, a.key[g]) == a.key + g;
   }

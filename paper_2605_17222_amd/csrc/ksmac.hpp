@@ -24,13 +24,14 @@ static_assert(kKsMacAlign == kThreads * kXcds, "ksmac grid: whole workgroups per
 // term's loads all in flight at once, a term ahead of their use: so the loops have no branch around a load: the
 // host pads absent plaintexts with a present one of the same term (masked to
 // zero), gives every term the same operands, and sorts the terms into
-// unrotated ones and groups of ni rotated terms that share a key; the pointers
+// unrotated ones and groups of rotated terms that share a key; the pointers
 // of a term come in with a few wide scalar loads.  The loads that run past the
 // last term go to one word of the launch's own operands (a cache hit).
 // Measured at N = 2^16, level 24 against loads behind per-operand branches
 // (a pointer load and its wait each): (4,4,4) 439 -> 397 us, (4,32,4) 3.31 ->
 // 2.78 ms, (1,16,4) 580 -> 581, packed 530 -> 486; (4,16,4) at N = 2^14,
-// level 13, 318 (with 16 terms a launch) -> 197 us.
+// level 13, 318 (with 16 terms a launch) -> 197 us.  A key read once per group,
+// whatever the group's size, against once per term: (3,7,3) 650 -> 453 us.
 
 // The launch's arguments where they are, in the kernel-argument segment: read
 // through a by-value parameter, kernels with more than 6 accumulators copied all
@@ -198,8 +199,7 @@ struct KsMacFoldInt {
 };
 
 // Layouts: KN / FN, the keys' / plaintexts' limb is packed narrow (32-bit and
-// 8-bit planes).  GROUPED: an even number a.ni of rotated terms per key, else
-// one.
+// 8-bit planes).  GROUPED: some rotated terms share a key, else each has its own.
 template <int NK, int MB, bool GROUPED, bool PK, bool PF, bool NARROW, typename Fold>
 __device__ __forceinline__ void ksmac_body(KsMacArgsK& a, const PrimeDev& pr, int l, uint32_t p, size_t n,
                                            int log_n, int alpha) {
@@ -214,7 +214,7 @@ __device__ __forceinline__ void ksmac_body(KsMacArgsK& a, const PrimeDev& pr, in
   Fold F(pr);
   KsMacTerm<NK, MB> t0, t1;
   KsMacKey<MB> key, key1;
-  const int ni = GROUPED ? a.ni : 1, groups = a.nr / ni;
+  const int groups = a.groups;
   uint32_t src = 0;
   if (groups > 0) {
     src = auto_index(p, a.gal[0], log_n);
@@ -269,12 +269,13 @@ __device__ __forceinline__ void ksmac_body(KsMacArgsK& a, const PrimeDev& pr, in
       fold(t1, a.nu + g + 1);
     }
   } else {
-    // two terms of a key per iteration; the last pair of a group loads the
+    // two terms of a key per iteration; the last one or two of a group load the
     // next key
     int m = a.nu;
     for (int g = 0; g < groups; ++g) {
       F.key(key);
-      for (int i = 2; i < ni; i += 2, m += 2) {
+      const int end = (int)(a.meta[m] >> kKsMacEnd);
+      for (; m + 2 < end; m += 2) {
         ksmac_load<NK, MB, FN>(t1, a, m + 1, src, p, n, w, true);
         __builtin_amdgcn_sched_barrier(0);
         fold(t0, m);
@@ -282,17 +283,22 @@ __device__ __forceinline__ void ksmac_body(KsMacArgsK& a, const PrimeDev& pr, in
         __builtin_amdgcn_sched_barrier(0);
         fold(t1, m + 1);
       }
-      ksmac_load<NK, MB, FN>(t1, a, m + 1, src, p, n, w, true);
-      __builtin_amdgcn_sched_barrier(0);
-      fold(t0, m);
+      if (m + 1 < end) {
+        ksmac_load<NK, MB, FN>(t1, a, m + 1, src, p, n, w, true);
+        __builtin_amdgcn_sched_barrier(0);
+        fold(t0, m);
+        t0 = t1;
+        ++m;
+      }
       const bool live = g + 1 < groups;
       const int g1 = live ? g + 1 : g;
       src = auto_index(p, a.gal[g1], log_n);
       ksmac_load_key<MB, KN>(key, a, g1, src, n, w, live);
-      ksmac_load<NK, MB, FN>(t0, a, live ? m + 2 : m, src, p, n, w, live);
+      ksmac_load<NK, MB, FN>(t1, a, live ? end : m, src, p, n, w, live);
       __builtin_amdgcn_sched_barrier(0);
-      fold(t1, m + 1);
-      m += 2;
+      fold(t0, m);
+      t0 = t1;
+      m = end;
     }
   }
   const size_t off = w.lo + p;
@@ -341,23 +347,25 @@ __global__ void __launch_bounds__(kThreads)
   }
 }
 
-template <int NK, int MB, bool GROUPED, bool PK, bool PF>
+template <int NK, int MB, bool PK, bool PF>
 void launch_ksmac_one(const ckks_params* P, const KsMacArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((ksmac_kernel<NK, MB, GROUPED, PK, PF>), dim3(P->n / kThreads, a.K), dim3(kThreads), 0, s, a,
-                     P->d_primes, P->log_n, P->alpha);
+  const dim3 grid(P->n / kThreads, a.K), block(kThreads);
+  if (a.groups < a.nr)
+    hipLaunchKernelGGL((ksmac_kernel<NK, MB, true, PK, PF>), grid, block, 0, s, a, P->d_primes, P->log_n, P->alpha);
+  else
+    hipLaunchKernelGGL((ksmac_kernel<NK, MB, false, PK, PF>), grid, block, 0, s, a, P->d_primes, P->log_n, P->alpha);
 }
 
 template <int NK, int MB>
 void launch_ksmac_mb(const ckks_params* P, const KsMacArgs& a, hipStream_t s) {
   if (a.key_packed && a.f_packed)
-    a.ni > 1 ? launch_ksmac_one<NK, MB, true, true, true>(P, a, s) : launch_ksmac_one<NK, MB, false, true, true>(P, a, s);
+    launch_ksmac_one<NK, MB, true, true>(P, a, s);
   else if (a.key_packed)
-    launch_ksmac_one<NK, MB, false, true, false>(P, a, s);
+    launch_ksmac_one<NK, MB, true, false>(P, a, s);
   else if (a.f_packed)
-    launch_ksmac_one<NK, MB, false, false, true>(P, a, s);
+    launch_ksmac_one<NK, MB, false, true>(P, a, s);
   else
-    a.ni > 1 ? launch_ksmac_one<NK, MB, true, false, false>(P, a, s)
-             : launch_ksmac_one<NK, MB, false, false, false>(P, a, s);
+    launch_ksmac_one<NK, MB, false, false>(P, a, s);
 }
 
 }  // namespace

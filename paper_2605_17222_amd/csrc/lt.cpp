@@ -656,15 +656,6 @@ void ksmac(Run& R, ThItem& it, const std::vector<int>& kk) {
     for (int i = 0; i < it.n1; ++i)
       if (it.used_m[it.n1 * j + i]) terms.push_back(Term{it.n1 * j + i, j, i});
   const int nk = (int)kk.size();
-  size_t nu = 0;  // unrotated terms, first
-  while (nu < terms.size() && terms[nu].j == 0) ++nu;
-  // An even number n1 of terms reads its key once if every rotation has all
-  // of its terms; otherwise each term reads its own (from L2 after the first).
-  int ni = it.n1 % 2 == 0 && it.n1 <= kMaxMacM / 2 && (int)nu == it.n1 && it.ks->packed == (it.D.packed && !it.D.z) ? it.n1 : 1;
-  std::vector<int> per_j(it.n2, 0);
-  for (const Term& t : terms) ++per_j[t.j];
-  for (int c : per_j)
-    if (c != 0 && c != it.n1) ni = 1;
   const int max_nm = it.D.z ? kMaxMacM : std::min(kMaxKsTerms, kMaxKsPts / nk);
   bool first = true;
   size_t t0 = 0;
@@ -672,7 +663,6 @@ void ksmac(Run& R, ThItem& it, const std::vector<int>& kk) {
     KsMacArgs a;
     memset(&a, 0, sizeof(a));
     a.nk = nk;
-    a.ni = ni;
     a.K = P->K(it.level);
     a.beta = P->beta(it.level);
     a.kmax = P->Kmax();
@@ -683,16 +673,18 @@ void ksmac(Run& R, ThItem& it, const std::vector<int>& kk) {
     const size_t mark = R.ws.mark();
     std::vector<EncItem> enc;
     size_t t = t0;
-    for (; t < terms.size(); ++t) {
+    int start = -1, last_j = 0;  // the current group's first term and its rotation
+    for (; t < terms.size() && a.nu + a.nr < max_nm; ++t) {
       const Term& tm = terms[t];
       const int m = a.nu + a.nr;
-      const bool group = tm.j == 0 || a.nr % ni == 0;  // a whole group fits, or none of it
-      if (m + (tm.j == 0 || !group ? 1 : ni) > max_nm) break;
-      if (tm.j != 0 && group) {
-        if (a.nr / ni == kMaxKsKeys) break;
+      if (tm.j != last_j) {
+        if (a.groups == kMaxKsKeys) break;
         const long r = it.stride * it.n1 * tm.j;
-        a.key[a.nr / ni] = it.ks->get(R, r);
-        a.gal[a.nr / ni] = galois(P, r);
+        a.key[a.groups] = it.ks->get(R, r);
+        a.gal[a.groups] = galois(P, r);
+        ++a.groups;
+        start = m;
+        last_j = tm.j;
       }
       a.a[m] = tm.i == 0 ? it.c0 : it.A[tm.i];
       a.db[m] = tm.j != 0 ? it.Dg[tm.i] : (tm.i == 0 ? it.c1 : it.B[tm.i]);
@@ -711,9 +703,10 @@ void ksmac(Run& R, ThItem& it, const std::vector<int>& kk) {
         a.f[m * nk + k] = any;
         a.meta[m] |= 1u << k;
       }
-      for (int k = 0; k < nk; ++k)  // a used term has a diagonal; absent ones repeat it, masked
+      for (int k = 0; k < nk; ++k)  // a used term has a diagonal; absent ones repeat it, masked out
         if (!(a.meta[m] >> k & 1)) a.f[m * nk + k] = any;
       ++(tm.j == 0 ? a.nu : a.nr);
+      if (start >= 0) a.meta[start] = (a.meta[start] & 0xffff) | (uint32_t)(m + 1) << kKsMacEnd;
     }
     for (size_t k = 0; k < kk.size(); ++k) {
       a.out0[k] = kk[k] >= 0 ? it.U0[kk[k]] : it.acc0;

@@ -68,13 +68,12 @@ __device__ __forceinline__ double as_d(uint64_t u) { return __longlong_as_double
 __device__ __forceinline__ uint64_t as_u(double d) { return (uint64_t)__double_as_longlong(d); }
 
 // The range of a launch that limb number `limb` falls in (a branch-free binary
-// search: a walk over up to 32 ranges costs a chain of dependent loads, which a
-// short workgroup notices: 21.6 -> 17.4 us for 320 limbs of 2^13).
+// search over as many steps as the launch has ranges: a walk over up to 32
+// ranges costs a chain of dependent loads, which a short workgroup notices:
+// 21.6 -> 17.4 us for 320 limbs of 2^13).
 __device__ __forceinline__ int find_range(const NttArgs& a, int limb) {
-  static_assert((kMaxRanges & (kMaxRanges - 1)) == 0, "binary search");
   int ri = 0;
-#pragma unroll
-  for (int step = kMaxRanges / 2; step > 0; step /= 2) ri += limb >= a.start[ri + step] ? step : 0;
+  for (int step = a.search; step > 0; step >>= 1) ri += limb >= a.start[ri + step] ? step : 0;
   return ri;
 }
 
@@ -619,6 +618,9 @@ hipError_t launch_ntt(const ckks_params* P, bool forward, const NttArgs& args, i
     at += i < a.nr ? a.r[i].count : 0;
   }
   if (at != total_limbs) return hipErrorInvalidValue;
+  static_assert((kMaxRanges & (kMaxRanges - 1)) == 0, "binary search");
+  a.search = 0;
+  for (int step = 1; step < a.nr; step *= 2) a.search = step;
   switch (P->log_n) {
     // Words per thread of the one-kernel transforms: a launch of at most a limb
     // per CU is bound by one workgroup's latency, so its limbs are spread over

@@ -149,3 +149,57 @@ def test_fused_launch_table_edges(case, split, drop):
     ppts = [None if f is None else H.ckks_pack(P, f) for f in dpts]
     assert np.array_equal(_single(c, split, ppts, pkeys, dct), ref)
     assert np.array_equal(_single(c, split, dpts, pkeys, dct), ref)
+
+
+@pytest.mark.parametrize("split", [(6, 3, 2), (3, 4, 2), (8, 4, 3), (4, 6, 5), (2, 12, 8)])
+def test_onfly_workspace_is_the_same_for_packed_keys(case, split):
+    """The workspace is asked for without keys, so the fused launches of
+    diagonals encoded on the fly must take the same workspace whether the keys
+    are packed or not: the size asked for serves both, with equal results."""
+    import torch
+    log("fused, on the fly, packed keys", split)
+    c = case
+    prm, level = c["prm"], c["level"]
+    P = gpu_params(prm)
+    n = split[0] * split[1] * split[2]
+    z = [torch.from_numpy(np.ascontiguousarray(d)).to("cuda")
+         for d in W.banded_diagonals(53, prm.slots, range(n)).values()]
+    dkeys = {r: H.to_device(k) for r, k in _keys(c, split).items()}
+    pkeys = {r: H.ckks_pack(P, k) for r, k in dkeys.items()}
+    dct = [H.to_device(c["ct"][0]), H.to_device(c["ct"][1])]
+    wsb = H.ckks_lt_workspace_size(P, level, split, z, H.CKKS_LT_TH_BSGS, onfly=True)
+    got = []
+    for keys in (dkeys, pkeys):
+        ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+        o0, o1 = H.empty((level, prm.n)), H.empty((level, prm.n))
+        H.ckks_lt_eval(P, level, c["delta"], dct[0], dct[1], split, z, c["delta"], keys, H.CKKS_LT_TH_BSGS, o0, o1,
+                       ws, wsb, onfly=True)
+        torch.cuda.synchronize()
+        got.append(np.stack([H.to_host(o0), H.to_host(o1)]))
+    assert np.array_equal(got[0], got[1])
+    zd = c["o"].decrypt_slots(got[0], c["delta"] * c["delta"] / prm.q[level])
+    ref = W.matvec(W.banded_diagonals(53, prm.slots, range(n)), c["v"])
+    assert np.abs(zd - ref).max() <= 5e-3 * n / 16
+
+
+@pytest.mark.parametrize("split,missing", [((4, 9, 1), (33, 34)), ((4, 9, 2), (4, 40, 68)), ((3, 7, 2), (3, 24)),
+                                           ((5, 5, 1), (24,)), ((4, 33, 1), (64, 128))])
+def test_fused_rotations_with_a_missing_term(case, split, missing):
+    """Rotations some of whose terms have no diagonal in any block (groups of
+    unequal size, split over launches), against the oracle's Algorithm 2."""
+    log("fused, missing terms", split, missing)
+    c = case
+    o, prm = c["o"], c["prm"]
+    inner = split[0] * split[1]
+    gone = {m % inner for m in missing}
+    diags = {d: z for d, z in W.banded_diagonals(59, prm.slots, range(inner * split[2])).items() if d % inner not in gone}
+    pts = o.th_plaintexts(diags, *split, c["delta"])
+    keys = _keys(c, split)
+    ref = o.lt_th(c["level"], c["ct"], split, pts, keys)
+    P = gpu_params(prm)
+    dpts = [None if f is None else H.to_device(f) for f in pts]
+    dkeys = {r: H.to_device(k) for r, k in keys.items()}
+    dct = [H.to_device(c["ct"][0]), H.to_device(c["ct"][1])]
+    assert np.array_equal(_single(c, split, dpts, dkeys, dct), ref)
+    ppts = [None if f is None else H.ckks_pack(P, f) for f in dpts]
+    assert np.array_equal(_single(c, split, ppts, {r: H.ckks_pack(P, k) for r, k in dkeys.items()}, dct), ref)
