@@ -101,7 +101,7 @@ __global__ void __launch_bounds__(256) enc_pass2(EncArgs a, const double* __rest
   }
   __syncthreads();
   lds_fft<LOGB>(lds[g], lane, tw, log_s);
-  const double scale = a.scale[it];
+  const double scale = a.scale;
   int64_t* __restrict__ coef = a.coef[it];
   // |scale u| beyond 2^62 is outside the documented range; clamp so the
   // conversion stays defined.

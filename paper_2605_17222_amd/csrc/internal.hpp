@@ -103,23 +103,27 @@ struct LimbRange {
   const uint64_t* sinv_sh;  // Shoup companion (device, inside a BConvPlan)
   int prime0;
   int count;
-  // Forward transforms: in holds N signed 64-bit coefficients shared by every
-  // limb of the range, reduced into each limb's prime as the first pass reads
-  // them (|coefficient| < 2^62).
-  int signed_in;
-  int pad;
 };
 
 constexpr int kMaxRanges = 32;
 struct NttArgs {
   int nr = 0;
-  // Set by the launch: where each range starts in the sequence of limbs and the
-  // first step of a binary search over them, or that every range covers the same
-  // primes and they are taken prime by prime.
-  int interleave = 0;
+  // Set by the launch: where each range starts in the sequence of limbs, and the
+  // first step of a binary search over them.
   int search = 0;
   int start[kMaxRanges];
   LimbRange r[kMaxRanges];
+};
+
+// Forward transforms of encoded plaintexts: item i's N signed coefficients
+// in[i] (|coefficient| < 2^62, reduced into each prime as the first pass reads
+// them) to `limbs` limbs at out[i], primes from prime0.
+constexpr int kMaxEnc = 128;
+struct NttSinArgs {
+  int items, limbs, prime0;
+  int interleave;  // set by the launch: limbs are taken prime by prime, not item by item
+  const int64_t* in[kMaxEnc];
+  uint64_t* out[kMaxEnc];
 };
 
 // Epilogue of the last forward pass: ModDown / rescale division step
@@ -250,17 +254,17 @@ class ProfScope {
 };
 
 // Plaintext encoding of up to kMaxEnc slot vectors per launch: z[i] holds
-// N/2 complex slots (re, im), encoded as rot(z, rot[i]) with scale[i]; y[i]
+// N/2 complex slots (re, im), encoded as rot(z, rot[i]) with `scale`; y[i]
 // is scratch for N/2 complex values; coef[i] receives the N coefficients.
-constexpr int kMaxEnc = 32;
 struct EncArgs {
   int count;
+  double scale;
   const double* z[kMaxEnc];
   int rot[kMaxEnc];
-  double scale[kMaxEnc];
   double* y[kMaxEnc];
   int64_t* coef[kMaxEnc];
 };
+static_assert(sizeof(EncArgs) <= 4096 - 64, "kernel arguments");
 
 // Device address of the no-allocation entry point's scratch array on
 // `device` (which must be current), looked up on first use and kept.
@@ -269,6 +273,7 @@ int scratch_address(int device, void** out);
 // Kernel launchers.
 hipError_t launch_ntt(const struct ::ckks_params* P, bool forward, const NttArgs& a, int total_limbs, int epi,
                       hipStream_t s);
+hipError_t launch_ntt_encoded(const struct ::ckks_params* P, const NttSinArgs& a, hipStream_t s);
 hipError_t launch_bconv(const struct ::ckks_params* P, const BConvArgs& a, int items, int ns, hipStream_t s);
 hipError_t launch_keyswitch(const struct ::ckks_params* P, const KsArgs& a, hipStream_t s);
 hipError_t launch_keyswitch_gather(const struct ::ckks_params* P, const KsGatherArgs& a, hipStream_t s);

@@ -54,8 +54,6 @@ LimbRange range(const uint64_t* in, uint64_t* out, int prime0, int count, const 
   r.sinv_sh = sinv_sh;
   r.prime0 = prime0;
   r.count = count;
-  r.signed_in = 0;
-  r.pad = 0;
   return r;
 }
 
@@ -372,34 +370,45 @@ struct EncItem {
   int64_t* coef;
 };
 
-// FFT passes and forward NTTs (from the signed integers) of up to kMaxEnc
-// items per launch.
-void encode(Run& R, const std::vector<EncItem>& items) {
+// FFT passes and forward NTTs (from the signed integers).  The FFT's scratch is
+// the item's first output limb; the integers of at most 64 items per launch
+// take workspace, those of more (up to kMaxEnc) the caller's `spare` limbs.
+// own_fft: the FFT's scratch is workspace too (outputs that overlap slots),
+// and 32 items share a launch.  All items of a call have the same scale and
+// primes.  128 items a launch instead of 32: dense Set-A (N = 2^13) 6.73 -> 4.63
+// ms, its launches of 320 limbs having left two thirds of the chip idle; at
+// N = 2^16, where 32 fill it, no difference (nor did launches small enough for
+// the last-level cache to hold the transform's intermediate gain anything).
+void encode(Run& R, const std::vector<EncItem>& items, const std::vector<uint64_t*>& spare = {},
+            bool own_fft = false) {
   const long S = R.P->n / 2;
-  for (size_t i0 = 0; i0 < items.size(); i0 += kMaxEnc) {
+  if (items.empty()) return;
+  const size_t per = own_fft ? 32 : std::min((size_t)kMaxEnc, spare.size() + 64);
+  for (size_t i0 = 0; i0 < items.size(); i0 += per) {
     const size_t mark = R.ws.mark();
-    const int cnt = (int)std::min<size_t>(kMaxEnc, items.size() - i0);
+    const int cnt = (int)std::min(per, items.size() - i0);
     EncArgs ea;
+    NttSinArgs na;
     memset(&ea, 0, sizeof(ea));
-    ea.count = cnt;
+    memset(&na, 0, sizeof(na));
+    ea.count = na.items = cnt;
+    ea.scale = items[0].scale;
+    na.prime0 = items[0].first_prime;
+    na.limbs = items[0].n_limbs;
+    size_t used = 0;
     for (int c = 0; c < cnt; ++c) {
       const EncItem& it = items[i0 + c];
       ea.z[c] = it.z;
       ea.rot[c] = (int)(((it.rot % S) + S) % S);
-      ea.scale[c] = it.scale;
-      ea.y[c] = reinterpret_cast<double*>(R.limbs(1));  // N/2 complex values
-      ea.coef[c] = it.coef ? it.coef : reinterpret_cast<int64_t*>(R.limbs(1));
+      ea.y[c] = reinterpret_cast<double*>(own_fft ? R.limbs(1) : it.out);  // N/2 complex values
+      ea.coef[c] = it.coef;
+      if (!it.coef) ea.coef[c] = reinterpret_cast<int64_t*>(used < spare.size() ? spare[used++] : R.limbs(1));
+      na.in[c] = ea.coef[c];
+      na.out[c] = it.out;
     }
     if (R.live()) {
       R.check(launch_encode_fft(R.P, ea, R.s));
-      // the NTT's first pass reduces the integers into each prime itself
-      NttBatch fwd(R, true);
-      for (int c = 0; c < cnt; ++c) {
-        const EncItem& it = items[i0 + c];
-        LimbRange r = range(reinterpret_cast<const uint64_t*>(ea.coef[c]), it.out, it.first_prime, it.n_limbs);
-        r.signed_in = 1;
-        fwd.add(r);
-      }
+      if (R.live()) R.check(launch_ntt_encoded(R.P, na, R.s));
     }
     R.ws.reset(mark);
   }
@@ -426,7 +435,8 @@ struct MacEnc {
 // reads them, into workspace that the next launch reuses.
 // f_packed: the resident plaintexts are packed PQ polynomials (prime_off 0).
 void ptmac(Run& R, int nlimbs, int prime_off, const std::vector<MacTerm>& terms, const std::vector<uint64_t*>& o0,
-           const std::vector<uint64_t*>& o1, const MacEnc* enc = nullptr, bool f_packed = false) {
+           const std::vector<uint64_t*>& o1, const MacEnc* enc = nullptr, bool f_packed = false,
+           const std::vector<uint64_t*>& spare = {}) {
   const int nk_all = (int)o0.size();
   for (int k0 = 0; k0 < nk_all; k0 += kMaxMacK) {
     const int nk = std::min(kMaxMacK, nk_all - k0);
@@ -467,7 +477,7 @@ void ptmac(Run& R, int nlimbs, int prime_off, const std::vector<MacTerm>& terms,
         ma.out0[k] = o0[k0 + k];
         ma.out1[k] = o1[k0 + k];
       }
-      encode(R, pts);
+      encode(R, pts, spare);
       if (R.live()) R.check(launch_ptmac(R.P, ma, R.s));
       R.ws.reset(mark);
       first = false;
@@ -645,7 +655,7 @@ bool fuse_middle(const ckks_params* P, const ThItem& it) {
 // slot vectors are encoded right before the launch that reads them (f^ =
 // encode(rot(z, -G_k))), into workspace the next launch reuses; their
 // launches stay at kMaxMacM terms, which bounds that workspace.
-void ksmac(Run& R, ThItem& it, const std::vector<int>& kk) {
+void ksmac(Run& R, ThItem& it, const std::vector<int>& kk, const std::vector<uint64_t*>& spare) {
   const ckks_params* P = R.P;
   const int inner = it.n1 * it.n2;
   struct Term {
@@ -712,7 +722,7 @@ void ksmac(Run& R, ThItem& it, const std::vector<int>& kk) {
       a.out0[k] = kk[k] >= 0 ? it.U0[kk[k]] : it.acc0;
       a.out1[k] = kk[k] >= 0 ? it.U1[kk[k]] : it.acc1;
     }
-    encode(R, enc);
+    encode(R, enc, spare);
     if (R.live()) R.check(launch_ksmac(P, a, R.s));
     R.ws.reset(mark);
     first = false;
@@ -827,8 +837,15 @@ void lt_th(Run& R, std::vector<ThItem>& items) {
     for (int k = 0; k < it.n3; ++k)
       if (k == it.kdir || it.used_k[k]) kk.push_back(k);
     if (it.kdir < 0) kk.push_back(-1);
+    // limbs that on-the-fly encoding may use until then: the outer layer's digits
+    std::vector<uint64_t*> spare;
+    if (it.D.z)
+      for (int k = 0; k < it.n3; ++k)
+        if (k != it.kdir && it.used_k[k])
+          for (size_t l = 0; l < (size_t)P->beta(it.level) * K && spare.size() < kMaxEnc; ++l)
+            spare.push_back(it.Dk[k] ? it.Dk[k] + l * R.N : nullptr);
     if (it.fused) {
-      ksmac(R, it, kk);
+      ksmac(R, it, kk, spare);
       continue;
     }
     std::vector<MacTerm> terms;
@@ -854,7 +871,7 @@ void lt_th(Run& R, std::vector<ThItem>& items) {
       o1.push_back(k >= 0 ? it.U1[k] : it.acc1);
       enc.rot.push_back(k >= 0 ? -it.giant(P, k) : 0);  // f^ = encode(rot(diag, -G_k))
     }
-    ptmac(R, K, 0, terms, o0, o1, it.D.z ? &enc : nullptr, it.D.packed);
+    ptmac(R, K, 0, terms, o0, o1, it.D.z ? &enc : nullptr, it.D.packed, spare);
   }
   // Lines 13-18: outer rotations by G_k: ModDown and Decompose of every
   // (item, k) at once, then per item one gather kernel adds
@@ -1284,13 +1301,29 @@ static int encode_common(const ckks_params* P, int count, const ckks_encode_item
     its.push_back(EncItem{items[i].slots, (long)items[i].rot, scale, first_prime, n_limbs, items[i].out,
                           plan_only ? nullptr : items[i].coef});
   }
+  // sized for the FFT's scratch in workspace, whether this call needs it or not
   Run D = make_run(P, stream, true, nullptr);
-  encode(D, its);
+  encode(D, its, {}, true);
   if (need) *need = D.ws.peak;
   if (plan_only) return CKKS_OK;
   if (D.ws.peak > ws_bytes || (D.ws.peak > 0 && !ws)) return CKKS_E_WORKSPACE;
+  // an output may hold slots that are still to be read (in place, or another
+  // item's): then no output serves as scratch
+  std::vector<std::pair<const uint8_t*, const uint8_t*>> in, out;
+  for (const EncItem& it : its) {
+    const uint8_t *z = reinterpret_cast<const uint8_t*>(it.z), *o = reinterpret_cast<const uint8_t*>(it.out);
+    in.push_back({z, z + (size_t)P->n * 8});
+    out.push_back({o, o + (size_t)n_limbs * P->n * 8});
+  }
+  std::sort(in.begin(), in.end());
+  std::sort(out.begin(), out.end());
+  bool shared = false;
+  for (size_t i = 0, o = 0; i < in.size() && o < out.size() && !shared;) {
+    shared = in[i].first < out[o].second && out[o].first < in[i].second;
+    in[i].second < out[o].second ? ++i : ++o;
+  }
   Run X = make_run(P, stream, false, ws);
-  encode(X, its);
+  encode(X, its, {}, shared);
   return X.err;
 }
 

@@ -40,6 +40,8 @@
 // 2^p - 1 for every row (the whole table, twice the limb's own bytes), so it
 // forms them instead as G[s][y] R[row][s] mod q from two small tables (the
 // factorisation is described at ntt_row_tables_size).
+#include <type_traits>
+
 #include "internal.hpp"
 #include "modarith.hpp"
 
@@ -76,6 +78,24 @@ __device__ __forceinline__ int find_range(const NttArgs& a, int limb) {
   for (int step = a.search; step > 0; step >>= 1) ri += limb >= a.start[ri + step] ? step : 0;
   return ri;
 }
+
+// The limb that workgroup row `y` of a launch works on: its range (kept in R,
+// limb numbers from 0).
+__device__ __forceinline__ int find_limb(const NttArgs& a, int y, LimbRange& R) {
+  const int ri = find_range(a, y);
+  R = a.r[ri];
+  return y - a.start[ri];
+}
+__device__ __forceinline__ int find_limb(const NttSinArgs& a, int y, LimbRange& R) {
+  const int item = a.interleave ? y % a.items : y / a.limbs;
+  R = LimbRange{};
+  R.in = reinterpret_cast<const uint64_t*>(a.in[item]);
+  R.out = a.out[item];
+  R.prime0 = a.prime0;
+  return a.interleave ? y / a.items : y % a.limbs;
+}
+template <bool SIN>
+using NttArgsOf = std::conditional_t<SIN, NttSinArgs, NttArgs>;
 
 // The arithmetic of one direction and path on a thread's NW words (integer
 // residues, or double bits on the FP path).
@@ -168,7 +188,7 @@ struct Butterflies {
 };
 
 // SIN (forward column pass only): the input is the range's shared signed
-// coefficients (LimbRange::signed_in).
+// coefficients (NttSinArgs).
 template <int PLOG, int G, bool COL, bool FWD, bool FP, bool SIN>
 __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const PrimeDev& pr, int log_n, int epi,
                                          uint64_t* lds, double* tws) {
@@ -180,7 +200,7 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
   const int n = 1 << log_n;
   const TableWords tw = (TableWords)(pr.tw + (FWD ? 0 : 2 * (size_t)n));
   const bool first = (COL == FWD);  // first pass of the transform
-  const uint64_t* __restrict__ src = (first ? R.in : R.out) + (SIN ? 0 : (size_t)limb * n);
+  const uint64_t* __restrict__ src = (first ? R.in : R.out) + ((SIN && COL) ? 0 : (size_t)limb * n);
   uint64_t* __restrict__ dst = R.out + (size_t)limb * n;
 
   const int tid = threadIdx.x;
@@ -272,7 +292,7 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
     for (int u = 0; u < 16; ++u) v[u] = L[lds_pad(layout1 ? (j + T * u) : (16 * j + u))];
   };
   if (FWD) {
-    if constexpr (SIN) {
+    if constexpr (SIN && COL) {
       const int64_t* __restrict__ sc = reinterpret_cast<const int64_t*>(src);
 #pragma unroll
       for (int u = 0; u < 16; ++u) v[u] = F.residue(sc[addr(j + T * u)]);
@@ -353,22 +373,13 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
 
 template <int PLOG, int G, bool COL, bool FWD, bool SIN>
 __global__ void __launch_bounds__(G*(1 << PLOG) / 16) __attribute__((amdgpu_waves_per_eu(COL ? 1 : 4)))
-    ntt_pass(NttArgs args, const PrimeDev* __restrict__ primes, int log_n, int epi) {
+    ntt_pass(NttArgsOf<SIN> args, const PrimeDev* __restrict__ primes, int log_n, int epi) {
   constexpr int P = 1 << PLOG;
   constexpr int RS = P + P / 16 + 1;
   __shared__ uint64_t lds[G * RS];
   __shared__ double tws[COL ? 1 : P + G * 2 * PLOG];  // FP row pass twiddle factors
-  // Which limb (uniform over the workgroup).
-  int limb = blockIdx.y;
-  int ri = 0;
-  if (args.interleave) {
-    ri = limb % args.nr;
-    limb /= args.nr;
-  } else {
-    ri = find_range(args, limb);
-    limb -= args.start[ri];
-  }
-  const LimbRange& R = args.r[ri];
+  LimbRange R;
+  const int limb = find_limb(args, blockIdx.y, R);  // uniform over the workgroup
   const PrimeDev& pr = primes[R.prime0 + limb];
   if (pr.fp)
     ntt_body<PLOG, G, COL, FWD, true, SIN>(R, limb, pr, log_n, epi, lds, tws);
@@ -516,12 +527,10 @@ __device__ __forceinline__ void ntt_full_body(const LimbRange& R, int limb, cons
 
 template <int LOGN, int LW, bool FWD, bool SIN>
 __global__ void __launch_bounds__(1 << (LOGN - LW)) __attribute__((amdgpu_waves_per_eu(4)))
-    ntt_full(NttArgs args, const PrimeDev* __restrict__ primes, int epi) {
+    ntt_full(NttArgsOf<SIN> args, const PrimeDev* __restrict__ primes, int epi) {
   __shared__ uint64_t lds[(1 << LOGN) + (1 << LOGN) / (1 << LW)];
-  int limb = blockIdx.x;
-  const int ri = find_range(args, limb);
-  limb -= args.start[ri];
-  const LimbRange& R = args.r[ri];
+  LimbRange R;
+  const int limb = find_limb(args, blockIdx.x, R);
   const PrimeDev& pr = primes[R.prime0 + limb];
   if (pr.fp)
     ntt_full_body<LOGN, LW, FWD, true, SIN>(R, limb, pr, epi, lds);
@@ -534,72 +543,82 @@ __global__ void __launch_bounds__(1 << (LOGN - LW)) __attribute__((amdgpu_waves_
 // limbs (4x the workgroups) was measured slower: the inverse column pass
 // over 9-10 limbs 0.106 -> 0.147 ms per (4,4,4) LT, its 32-byte column
 // segments costing more than the extra workgroups gain.
-// Row passes of ranges over the same integer-path primes (the plaintexts of an
-// encoding launch) are taken prime by prime, not range by range: such a pass
-// reads twice as many twiddle words as data words, and this way they come from
-// L2 after the first range (44 limbs of 54 bits x 32 plaintexts at N = 2^16:
-// 369 -> 325 us; FP64-path limbs read small tables and are better off range by
-// range, as are column passes, whose input all limbs of a range share).
-template <int PLOG, bool COL, bool FWD>
-hipError_t launch_pass(const ckks_params* P, NttArgs& a, int total, int epi, hipStream_t s) {
+template <int PLOG, bool COL, bool FWD, bool SIN>
+hipError_t launch_pass(const ckks_params* P, const NttArgsOf<SIN>& a, int total, double words, int epi,
+                       hipStream_t s) {
   constexpr int Pn = 1 << PLOG;
   constexpr int G = 4096 / Pn;
-  const int n = P->n;
-  const int subs = n >> PLOG;  // columns (column pass) or rows
+  const int subs = P->n >> PLOG;  // columns (column pass) or rows
   if (subs % G) return hipErrorInvalidValue;
-  dim3 grid(subs / G, total);
-  const int id = FWD ? (COL ? CKKS_KERNEL_NTT_FWD_COL : CKKS_KERNEL_NTT_FWD_ROW)
-                     : (COL ? CKKS_KERNEL_NTT_INV_COL : CKKS_KERNEL_NTT_INV_ROW);
-  double words = (double)total * n * (epi == EPI_SUBMUL ? 3 : 2);
-  if (!FWD && !COL)
-    for (int i = 0; i < a.nr; ++i) words += a.r[i].copy ? (double)a.r[i].count * n : 0;
-  const bool sin = a.r[0].signed_in != 0;
-  a.interleave = !COL && a.nr > 1;
-  for (int i = 0; i < a.nr; ++i)
-    if (a.r[i].prime0 != a.r[0].prime0 || a.r[i].count != a.r[0].count) a.interleave = 0;
-  for (int l = 0; l < a.r[0].count; ++l)
-    if (P->primes[a.r[0].prime0 + l] < kFpPrimeLimit) a.interleave = 0;
-  ProfScope prof(id, s, words * 8);
-  if constexpr (COL && FWD) {
-    if (sin) {
-      hipLaunchKernelGGL((ntt_pass<PLOG, G, COL, FWD, true>), grid, dim3(G * Pn / 16), 0, s, a, P->d_primes,
-                         P->log_n, epi);
-      return hipGetLastError();
-    }
-  }
-  hipLaunchKernelGGL((ntt_pass<PLOG, G, COL, FWD, false>), grid, dim3(G * Pn / 16), 0, s, a, P->d_primes,
-                     P->log_n, epi);
+  ProfScope prof(FWD ? (COL ? CKKS_KERNEL_NTT_FWD_COL : CKKS_KERNEL_NTT_FWD_ROW)
+                     : (COL ? CKKS_KERNEL_NTT_INV_COL : CKKS_KERNEL_NTT_INV_ROW),
+                 s, words * P->n * 8);
+  hipLaunchKernelGGL((ntt_pass<PLOG, G, COL, FWD, SIN>), dim3(subs / G, total), dim3(G * Pn / 16), 0, s, a,
+                     P->d_primes, P->log_n, epi);
   return hipGetLastError();
 }
 
+// Words moved per coefficient position: a read and a write of each limb, the
+// kept limbs of the division epilogue, the copies of an inverse transform.
+double words_of(const NttArgs& a, int total, int epi, bool copies) {
+  double words = (double)total * (epi == EPI_SUBMUL ? 3 : 2);
+  if (copies)
+    for (int i = 0; i < a.nr; ++i) words += a.r[i].copy ? a.r[i].count : 0;
+  return words;
+}
+
 template <int PA, int PB>
-hipError_t launch_both(const ckks_params* P, bool forward, NttArgs& a, int total, int epi, hipStream_t s) {
+hipError_t launch_both(const ckks_params* P, bool forward, const NttArgs& a, int total, int epi, hipStream_t s) {
   hipError_t e;
   if (forward) {
-    e = launch_pass<PA, true, true>(P, a, total, EPI_NONE, s);
+    e = launch_pass<PA, true, true, false>(P, a, total, words_of(a, total, EPI_NONE, false), EPI_NONE, s);
     if (e != hipSuccess) return e;
-    return launch_pass<PB, false, true>(P, a, total, epi, s);
+    return launch_pass<PB, false, true, false>(P, a, total, words_of(a, total, epi, false), epi, s);
   }
-  e = launch_pass<PB, false, false>(P, a, total, EPI_NONE, s);
+  e = launch_pass<PB, false, false, false>(P, a, total, words_of(a, total, EPI_NONE, true), EPI_NONE, s);
   if (e != hipSuccess) return e;
-  return launch_pass<PA, true, false>(P, a, total, EPI_NONE, s);
+  return launch_pass<PA, true, false, false>(P, a, total, words_of(a, total, EPI_NONE, false), EPI_NONE, s);
+}
+
+// Row passes of encoded plaintexts over integer-path primes are taken prime by
+// prime, not item by item: such a pass reads twice as many twiddle words as
+// data words, and this way they come from L2 after the first item (44 limbs of
+// 54 bits x 32 plaintexts at N = 2^16: 369 -> 325 us; FP64-path limbs read small
+// tables and are better off item by item, as are column passes, whose input all
+// limbs of an item share).
+template <int PA, int PB>
+hipError_t launch_both_encoded(const ckks_params* P, NttSinArgs a, hipStream_t s) {
+  const int total = a.items * a.limbs;
+  a.interleave = 0;
+  hipError_t e = launch_pass<PA, true, true, true>(P, a, total, total + a.items, EPI_NONE, s);
+  if (e != hipSuccess) return e;
+  a.interleave = 1;
+  for (int l = 0; l < a.limbs; ++l)
+    if (P->primes[a.prime0 + l] < kFpPrimeLimit) a.interleave = 0;
+  return launch_pass<PB, false, true, true>(P, a, total, 2.0 * total, EPI_NONE, s);
 }
 
 // The whole transform in one launch.  Timed as the column pass of its
 // direction.
-template <int LOGN, int LW>
-hipError_t launch_full(const ckks_params* P, bool forward, const NttArgs& a, int total, int epi, hipStream_t s) {
-  double words = (double)total * P->n * (epi == EPI_SUBMUL ? 3 : 2);
-  for (int i = 0; i < a.nr; ++i) words += a.r[i].copy ? (double)a.r[i].count * P->n : 0;
-  ProfScope prof(forward ? CKKS_KERNEL_NTT_FWD_COL : CKKS_KERNEL_NTT_INV_COL, s, words * 8);
-  const dim3 grid(total), block(1 << (LOGN - LW));
-  if (!forward)
-    hipLaunchKernelGGL((ntt_full<LOGN, LW, false, false>), grid, block, 0, s, a, P->d_primes, epi);
-  else if (a.r[0].signed_in)
-    hipLaunchKernelGGL((ntt_full<LOGN, LW, true, true>), grid, block, 0, s, a, P->d_primes, epi);
-  else
-    hipLaunchKernelGGL((ntt_full<LOGN, LW, true, false>), grid, block, 0, s, a, P->d_primes, epi);
+template <int LOGN, int LW, bool FWD, bool SIN>
+hipError_t launch_full(const ckks_params* P, const NttArgsOf<SIN>& a, int total, double words, int epi,
+                       hipStream_t s) {
+  ProfScope prof(FWD ? CKKS_KERNEL_NTT_FWD_COL : CKKS_KERNEL_NTT_INV_COL, s, words * P->n * 8);
+  hipLaunchKernelGGL((ntt_full<LOGN, LW, FWD, SIN>), dim3(total), dim3(1 << (LOGN - LW)), 0, s, a, P->d_primes, epi);
   return hipGetLastError();
+}
+
+// Words per thread of the one-kernel transforms: a launch of at most a limb per
+// CU is bound by one workgroup's latency, so its limbs are spread over more
+// waves (8 words a thread against 16: 16 -> 12 us a transform of 2^12, 20 -> 18
+// us of 2^13); larger ones run faster with fewer exchanges (1280 limbs of 2^13:
+// 33 -> 29 us per 320).
+template <bool FWD, bool SIN>
+hipError_t launch_one_kernel(const ckks_params* P, const NttArgsOf<SIN>& a, int total, double words, int epi,
+                             hipStream_t s) {
+  if (P->log_n == 12) return launch_full<12, 3, FWD, SIN>(P, a, total, words, epi, s);
+  if (total <= 256) return launch_full<13, 3, FWD, SIN>(P, a, total, words, epi, s);
+  return launch_full<13, 4, FWD, SIN>(P, a, total, words, epi, s);
 }
 
 }  // namespace
@@ -608,10 +627,6 @@ hipError_t launch_ntt(const ckks_params* P, bool forward, const NttArgs& args, i
                       hipStream_t s) {
   if (total_limbs <= 0) return hipSuccess;
   NttArgs a = args;
-  // signed input: every range of the launch or none, forward transforms only
-  for (int i = 0; i < a.nr; ++i)
-    if ((a.r[i].signed_in != 0) != (a.r[0].signed_in != 0) || (a.r[i].signed_in && !forward))
-      return hipErrorInvalidValue;
   int at = 0;
   for (int i = 0; i < kMaxRanges; ++i) {
     a.start[i] = i < a.nr ? at : INT32_MAX;
@@ -622,18 +637,29 @@ hipError_t launch_ntt(const ckks_params* P, bool forward, const NttArgs& args, i
   a.search = 0;
   for (int step = 1; step < a.nr; step *= 2) a.search = step;
   switch (P->log_n) {
-    // Words per thread of the one-kernel transforms: a launch of at most a limb
-    // per CU is bound by one workgroup's latency, so its limbs are spread over
-    // more waves (8 words a thread against 16: 16 -> 12 us a transform of 2^12,
-    // 20 -> 18 us of 2^13); larger ones run faster with fewer exchanges (1280
-    // limbs of 2^13: 33 -> 29 us per 320).
-    case 12: return launch_full<12, 3>(P, forward, a, total_limbs, epi, s);
-    case 13:
-      return total_limbs <= 256 ? launch_full<13, 3>(P, forward, a, total_limbs, epi, s)
-                                : launch_full<13, 4>(P, forward, a, total_limbs, epi, s);
+    case 12:
+    case 13: {
+      const double words = words_of(a, total_limbs, epi, true);
+      return forward ? launch_one_kernel<true, false>(P, a, total_limbs, words, epi, s)
+                     : launch_one_kernel<false, false>(P, a, total_limbs, words, epi, s);
+    }
     case 14: return launch_both<7, 7>(P, forward, a, total_limbs, epi, s);
     case 15: return launch_both<8, 7>(P, forward, a, total_limbs, epi, s);
     case 16: return launch_both<8, 8>(P, forward, a, total_limbs, epi, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_ntt_encoded(const ckks_params* P, const NttSinArgs& a, hipStream_t s) {
+  if (a.items < 1 || a.items > kMaxEnc || a.limbs < 1 || a.prime0 < 0 || a.prime0 + a.limbs > P->Kmax())
+    return hipErrorInvalidValue;
+  const int total = a.items * a.limbs;
+  switch (P->log_n) {
+    case 12:
+    case 13: return launch_one_kernel<true, true>(P, a, total, total + a.items, EPI_NONE, s);
+    case 14: return launch_both_encoded<7, 7>(P, a, s);
+    case 15: return launch_both_encoded<8, 7>(P, a, s);
+    case 16: return launch_both_encoded<8, 8>(P, a, s);
     default: return hipErrorInvalidValue;
   }
 }
