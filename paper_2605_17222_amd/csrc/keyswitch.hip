@@ -306,8 +306,8 @@ struct MacOps {
 // Index m's operands: (a_m, b_m) (for m = 0 with P c', the raw c' words) and
 // the NK plaintext words (0 where a plaintext is absent).
 template <int NK, bool PACKED, bool NARROW, typename PrimeT>
-__device__ __forceinline__ void mac_load(MacOps<NK>& o, const MacArgs& a, const PrimeT& pr, int m, int l, size_t p,
-                                         size_t n, int alpha, size_t fo) {
+__device__ __forceinline__ void mac_load(MacOps<NK>& o, const MacArgs& a, int kz, const PrimeT& pr, int m, int l,
+                                         size_t p, size_t n, int alpha, size_t fo) {
   const size_t off = (size_t)l * n + p;
   if (m == 0 && a.pscaled0) {
     const int lq = l + a.prime_off - alpha;
@@ -319,7 +319,7 @@ __device__ __forceinline__ void mac_load(MacOps<NK>& o, const MacArgs& a, const 
   }
 #pragma unroll
   for (int k = 0; k < NK; ++k) {
-    const uint64_t* __restrict__ fp = a.f[k][m];
+    const uint64_t* __restrict__ fp = a.f[kz + k][m];
     o.f[k] = 0;
     if (fp) {
       if constexpr (PACKED)
@@ -336,14 +336,14 @@ __device__ __forceinline__ void mac_load(MacOps<NK>& o, const MacArgs& a, const 
 // flight across iterations.  fo: byte offset of the limb within each
 // plaintext.
 template <int NK, bool PACKED, bool NARROW, typename PrimeT>
-__device__ __forceinline__ void mac_loop(const MacArgs& a, const PrimeT& pr, int l, size_t p, size_t n, int alpha,
+__device__ __forceinline__ void mac_loop(const MacArgs& a, int kz, const PrimeT& pr, int l, size_t p, size_t n, int alpha,
                                          size_t fo, U128 (&x)[NK], U128 (&y)[NK]) {
   const uint64_t q = pr.q;
   if (a.nm <= 0) return;
   MacOps<NK> cur{}, nxt{};
-  mac_load<NK, PACKED, NARROW>(cur, a, pr, 0, l, p, n, alpha, fo);
+  mac_load<NK, PACKED, NARROW>(cur, a, kz, pr, 0, l, p, n, alpha, fo);
   for (int m = 0; m < a.nm; ++m) {
-    if (m + 1 < a.nm) mac_load<NK, PACKED, NARROW>(nxt, a, pr, m + 1, l, p, n, alpha, fo);
+    if (m + 1 < a.nm) mac_load<NK, PACKED, NARROW>(nxt, a, kz, pr, m + 1, l, p, n, alpha, fo);
     uint64_t av = cur.a, bv = cur.b;
     if (m == 0 && a.pscaled0) {
       // (a_0, b_0) = (P c0', P c1'): zero on the special primes.
@@ -352,7 +352,7 @@ __device__ __forceinline__ void mac_loop(const MacArgs& a, const PrimeT& pr, int
     }
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
-      if (a.f[k][m]) {
+      if (a.f[kz + k][m]) {
         add128(x[k], mul_wide(av, cur.f[k]));
         add128(y[k], mul_wide(bv, cur.f[k]));
       }
@@ -364,7 +364,7 @@ __device__ __forceinline__ void mac_loop(const MacArgs& a, const PrimeT& pr, int
 // The MAC loop for packed plaintexts: two iterations unrolled (the packed
 // loads take more registers, and a pipelined loop would cost a wave).
 template <int NK, bool NARROW, typename PrimeT>
-__device__ __forceinline__ void mac_loop_packed(const MacArgs& a, const PrimeT& pr, int l, size_t p, size_t n,
+__device__ __forceinline__ void mac_loop_packed(const MacArgs& a, int kz, const PrimeT& pr, int l, size_t p, size_t n,
                                                 int alpha, size_t fo, U128 (&x)[NK], U128 (&y)[NK]) {
   const uint64_t q = pr.q;
   const size_t off = (size_t)l * n + p;
@@ -382,7 +382,7 @@ __device__ __forceinline__ void mac_loop_packed(const MacArgs& a, const PrimeT& 
     }
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
-      const uint64_t* __restrict__ fp = a.f[k][m];
+      const uint64_t* __restrict__ fp = a.f[kz + k][m];
       if (fp) {
         const uint64_t f = ld_word<NARROW>(reinterpret_cast<const uint8_t*>(fp) + fo, p, n);
         add128(x[k], mul_wide(av, f));
@@ -400,6 +400,7 @@ __global__ void __launch_bounds__(kThreads)
   const size_t n = (size_t)1 << log_n;
   const size_t p = (size_t)blockIdx.x * kThreads + threadIdx.x;
   const int l = blockIdx.y;
+  const int kz = blockIdx.z * NK;  // this workgroup's first accumulator
   const PrimeDev& pr = primes[l + a.prime_off];
   const uint64_t q = pr.q;
   const size_t off = (size_t)l * n + p;
@@ -410,28 +411,28 @@ __global__ void __launch_bounds__(kThreads)
   for (int k = 0; k < NK; ++k) x[k] = y[k] = U128{0, 0};
   if constexpr (F_PACKED) {
     if (pr.narrow)
-      mac_loop_packed<NK, true>(a, pr, l, p, n, alpha, fo, x, y);
+      mac_loop_packed<NK, true>(a, kz, pr, l, p, n, alpha, fo, x, y);
     else
-      mac_loop_packed<NK, false>(a, pr, l, p, n, alpha, fo, x, y);
+      mac_loop_packed<NK, false>(a, kz, pr, l, p, n, alpha, fo, x, y);
   } else {
-    mac_loop<NK, false, false>(a, pr, l, p, n, alpha, fo, x, y);
+    mac_loop<NK, false, false>(a, kz, pr, l, p, n, alpha, fo, x, y);
   }
 #pragma unroll
   for (int k = 0; k < NK; ++k) {
     uint64_t xr = barrett128(x[k], q, pr.r_lo, pr.r_hi);
     uint64_t yr = barrett128(y[k], q, pr.r_lo, pr.r_hi);
     if (a.accumulate) {
-      xr = add_mod(xr, a.out0[k][off], q);
-      yr = add_mod(yr, a.out1[k][off], q);
+      xr = add_mod(xr, a.out0[kz + k][off], q);
+      yr = add_mod(yr, a.out1[kz + k][off], q);
     }
-    __builtin_nontemporal_store(xr, a.out0[k] + off);
-    __builtin_nontemporal_store(yr, a.out1[k] + off);
+    __builtin_nontemporal_store(xr, a.out0[kz + k] + off);
+    __builtin_nontemporal_store(yr, a.out1[kz + k] + off);
   }
 }
 
 template <int NK>
 hipError_t launch_mac(const ckks_params* P, const MacArgs& a, hipStream_t s) {
-  dim3 grid(P->n / kThreads, a.K);
+  dim3 grid(P->n / kThreads, a.K, a.nk / NK);
   if (a.f_packed)
     hipLaunchKernelGGL((mac_kernel<NK, true>), grid, dim3(kThreads), 0, s, a, P->d_primes, P->log_n, P->alpha);
   else
@@ -521,7 +522,14 @@ hipError_t launch_ptmac(const ckks_params* P, const MacArgs& a, hipStream_t s) {
     for (int m = 0; m < a.nm; ++m) nf += a.f[k][m] ? 1 : 0;
   const double words = (double)a.K * P->n * (2.0 * a.nm + 2.0 * a.nk * (a.accumulate ? 2 : 1));
   ProfScope prof(CKKS_KERNEL_PTMAC, s, words * 8 + nf * limb_bytes(P, a.K, a.f_packed && a.prime_off == 0));
-  switch (a.nk) {
+  // A launch of few workgroups (small N) splits the accumulators over more, down
+  // to two each, until there are 4 per CU; the (a_m, b_m) they then read again
+  // come from cache.  8 accumulators at N = 2^13, 10 limbs (320 workgroups):
+  // 42 -> 26 us (at 1472 workgroups splitting is slower: 135 -> 171 us per two
+  // launches).
+  int per = a.nk;
+  while (per % 2 == 0 && per > 2 && (int64_t)P->n / kThreads * a.K * (a.nk / per) < 1024) per /= 2;
+  switch (per) {
     case 1: return launch_mac<1>(P, a, s);
     case 2: return launch_mac<2>(P, a, s);
     case 3: return launch_mac<3>(P, a, s);
