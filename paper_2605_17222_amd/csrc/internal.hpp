@@ -46,6 +46,7 @@ struct PrimeDev {
   int narrow;              // q < 2^40: packed as a 32-bit and an 8-bit plane
   int bs_shift;            // bits(q) - 1 and floor(2^(64 + bs_shift) / q): barrett_sum
   uint64_t bs_mu;
+  uint64_t above62;        // the least multiple of q above 2^62
 };
 
 // Packed storage of resident operands (keys, plaintexts): a limb of a prime

@@ -250,6 +250,7 @@ int params_create(const ckks_params_desc* d, ckks_params** out) {
     c.pmod_sh = shoup_of(c.pmod, q);
     c.narrow = q < kNarrowLimit ? 1 : 0;
     c.pk_off = P->pk_poly_bytes;
+    c.above62 = ((1ull << 62) / q + 1) * q;
     c.bs_shift = 63 - __builtin_clzll(q);
     c.bs_mu = (uint64_t)(((u128)1 << (64 + c.bs_shift)) / q);
     P->pk_poly_bytes += (uint64_t)n * (c.narrow ? 5 : 8);

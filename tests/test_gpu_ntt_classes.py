@@ -82,3 +82,29 @@ def test_one_kernel_transform_shapes_agree():
     torch.cuda.synchronize()
     for it, ref in zip(items, alone):
         assert np.array_equal(np.stack([H.to_host(it.out0), H.to_host(it.out1)]), ref)
+
+
+@pytest.mark.parametrize("log_n", [12, 13, 14, 16])
+def test_encoded_integers_every_prime_class(log_n):
+    """The transform of an encoding's signed integers for every class of prime:
+    ordinary ones, and ones clamped at the ends of the range (+-2^62)."""
+    import torch
+    log("encoded integers, prime classes", log_n)
+    prm = _params(log_n)
+    o = O.Oracle(prm)
+    P = gpu_params(prm)
+    K, n = len(o.pq), prm.n
+    g = torch.Generator(device="cuda")
+    g.manual_seed(17)
+    z = torch.view_as_complex(torch.empty((n // 2, 2), dtype=torch.float64, device="cuda").uniform_(-1.0, 1.0,
+                                                                                                 generator=g))
+    wsb = H.ckks_encode_workspace_size(P, 1)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    for scale in (2.0 ** 30, 2.0 ** 66, 2.0 ** 200):
+        out, coef = H.empty((K, n)), H.empty((n,))
+        H.ckks_encode(P, [z], [3], scale, 0, K, [out], ws, wsb, coefs=[coef])
+        torch.cuda.synchronize()
+        m = coef.cpu().numpy()
+        if scale > 2.0 ** 100:
+            assert m.max() == 2 ** 62 and m.min() == -2 ** 62
+        assert np.array_equal(H.to_host(out), o.ntt(o.poly_from_signed(m, range(K)), range(K)))
