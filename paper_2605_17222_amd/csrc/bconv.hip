@@ -43,12 +43,27 @@ __global__ void __launch_bounds__(kThreads)
   const int m1 = max(m0, min(plan->nd, m0 + chunk));
   const int cnt = m1 - m0;  // 0 .. chunk <= kChunk
 
+  // Every source word is asked for at once, before the staging below, and no
+  // load of the kernel sits behind a branch or on another's result inside a
+  // loop: with a test of nsi around each source's load, and its constants and
+  // prime read there, a workgroup waited for NS loads one after the other
+  // (the three conversions of a rotation at N = 2^15, level 17: 38.8 -> 30.9 us;
+  // the six of a (4,4,4) LT at N = 2^14, level 13: 81.7 -> 67.8; at N = 2^16,
+  // level 24, where more workgroups hide it: 222 -> 208).  An item with fewer
+  // source limbs than the launch's NS (a digit group shorter than alpha) reads
+  // its first again, times the constant 0.
+  const int nsi = plan->ns;
+  uint64_t v[NS];
+#pragma unroll
+  for (int j = 0; j < NS; ++j) v[j] = src[(size_t)(j < nsi ? j : 0) * n + p];
+
   // The chunk's constants and primes, staged once per workgroup: read from
   // global memory inside the destination loop they would make every
   // iteration wait for a load.
   __shared__ uint64_t cst[kChunk][NS];
   __shared__ uint32_t cst2[kChunk][NS][2];
-  __shared__ uint64_t qd[kChunk][2];
+  __shared__ uint64_t qd[kChunk][2], sv[kChunk][2], hs[NS][3];
+  __shared__ uint32_t lim[kChunk];
   const int tid = (int)threadIdx.x;
   for (int e = tid; e < cnt * NS; e += kThreads) {
     const int mm = e / NS, j = e % NS;
@@ -56,53 +71,55 @@ __global__ void __launch_bounds__(kThreads)
     cst2[mm][j][0] = plan->hk[m0 + mm][j][0];
     cst2[mm][j][1] = plan->hk[m0 + mm][j][1];
   }
-  for (int e = tid; e < cnt; e += kThreads) {
-    const PrimeDev& pd = primes[plan->dst[m0 + e]];
-    qd[e][0] = pd.q;
-    qd[e][1] = pd.qinv_neg;
+  if (tid < cnt) {
+    const int di = plan->dst[m0 + tid];
+    const PrimeDev& pd = primes[di];
+    lim[tid] = (uint32_t)(di - shift);
+    qd[tid][0] = pd.q;
+    qd[tid][1] = pd.qinv_neg;
+    sv[tid][0] = plan->sinv[m0 + tid];
+    sv[tid][1] = plan->sinv_sh[m0 + tid];
+  } else if (tid >= kThreads - NS) {
+    const int e = tid - (kThreads - NS), j = e < nsi ? e : 0;
+    hs[e][0] = e < nsi ? plan->hinv[j] : 0;
+    hs[e][1] = e < nsi ? plan->hinv_sh[j] : 0;
+    hs[e][2] = primes[plan->src[j]].q;
   }
   __syncthreads();
 
-  // An item with fewer source limbs than the launch's NS (a digit group
-  // shorter than alpha) has zeros in the remaining places: every product
-  // with them vanishes.
-  const int nsi = plan->ns;
-  auto yj = [&](int j) -> uint64_t {
-    return j < nsi ? shoup(src[(size_t)j * n + p], plan->hinv[j], plan->hinv_sh[j], primes[plan->src[j]].q) : 0;
-  };
+#pragma unroll
+  for (int j = 0; j < NS; ++j) v[j] = shoup(v[j], hs[j][0], hs[j][1], hs[j][2]);
+  // The inner product of destination m, reduced.
+  uint32_t y0[S30 ? NS : 1], y1[S30 ? NS : 1];
   if constexpr (S30) {
-    // all primes below 2^60: the inner product from 30-bit column sums
-    uint32_t y0[NS], y1[NS];
+    // all primes below 2^60: from 30-bit column sums
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
-      const uint64_t v = yj(j);
-      y0[j] = (uint32_t)(v & ((1ull << 30) - 1));
-      y1[j] = (uint32_t)(v >> 30);
+      y0[j] = (uint32_t)(v[j] & ((1ull << 30) - 1));
+      y1[j] = (uint32_t)(v[j] >> 30);
     }
-    for (int m = m0; m < m1; ++m) {
-      const int di = plan->dst[m];
-      const size_t o = (size_t)(di - shift) * n + p;
-      const uint64_t q = qd[m - m0][0];
-      uint64_t v = redc(dot_split30<NS>(y0, y1, cst2[m - m0]), q, qd[m - m0][1]);
-      if (aux) v = shoup(aux[o] - v + q, plan->sinv[m], plan->sinv_sh[m], q);
-      dst[o] = v;
-    }
-    return;
   }
-  uint64_t y[NS];
+  auto dot = [&](int m) -> uint64_t {
+    if constexpr (S30) {
+      return redc(dot_split30<NS>(y0, y1, cst2[m]), qd[m][0], qd[m][1]);
+    } else {
+      const uint64_t* c = cst[m];
+      U128 acc = mul_wide(v[0], c[0]);
 #pragma unroll
-  for (int j = 0; j < NS; ++j) y[j] = yj(j);
-  for (int m = m0; m < m1; ++m) {
-    const int di = plan->dst[m];
-    const size_t o = (size_t)(di - shift) * n + p;
-    const uint64_t q = qd[m - m0][0], qn = qd[m - m0][1];
-    const uint64_t* c = cst[m - m0];
-    U128 acc = mul_wide(y[0], c[0]);
-#pragma unroll
-    for (int j = 1; j < NS; ++j) add128(acc, mul_wide(y[j], c[j]));
-    uint64_t v = redc(acc, q, qn);
-    if (aux) v = shoup(aux[o] - v + q, plan->sinv[m], plan->sinv_sh[m], q);
-    dst[o] = v;
+      for (int j = 1; j < NS; ++j) add128(acc, mul_wide(v[j], c[j]));
+      return redc(acc, qd[m][0], qd[m][1]);
+    }
+  };
+  if (aux) {
+    // the kept limbs' words, one destination ahead
+    uint64_t x = cnt > 0 ? aux[lim[0] * n + p] : 0;
+    for (int m = 0; m < cnt; ++m) {
+      const uint64_t cur = x;
+      x = aux[lim[min(m + 1, cnt - 1)] * n + p];
+      dst[lim[m] * n + p] = shoup(cur - dot(m) + qd[m][0], sv[m][0], sv[m][1], qd[m][0]);
+    }
+  } else {
+    for (int m = 0; m < cnt; ++m) dst[lim[m] * n + p] = dot(m);
   }
 }
 
