@@ -75,28 +75,43 @@ __host__ __device__ __forceinline__ uint64_t barrett128(U128 x, uint64_t q, uint
   return csub(x.lo - qhat * q, q);
 }
 
+// Carries in inline assembly.  On gfx950 a vector instruction that reads a mask (a
+// carry, a select) has to come at least two wait states after the vector
+// instruction that wrote it.  The compiler keeps that distance between its own
+// instructions but does not look into asm statements (between two of them it left
+// one, or none), so a mask is read in the statement that wrote it, with the
+// distance kept there, or in a later one behind two wait states of its own.
+
 // acc += a b for a, b < 2^61 (the cross products' sum stays below 2^63):
 // four multiply-adds and one carry chain, against fifteen instructions for
 // mul_wide and add128.
 __host__ __device__ __forceinline__ void mac128(U128& acc, uint64_t a, uint64_t b) {
-#ifdef __HIP_DEVICE_COMPILE__
   const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32);
   const uint32_t b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
   uint64_t m = (uint64_t)a0 * b1;
   m += (uint64_t)a1 * b0;
   const uint64_t hi = acc.hi + (uint64_t)a1 * b1;
-  uint64_t lo = acc.lo, c, d;
+  uint64_t lo = acc.lo;
+#ifdef __HIP_DEVICE_COMPILE__
+  uint64_t c, d;
   asm("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(lo), "=s"(c) : "v"(a0), "v"(b0));
-  uint32_t mh, w1, w2, w3;
-  asm("v_addc_co_u32_e64 %0, %1, 0, %2, %3" : "=v"(mh), "=s"(d) : "v"((uint32_t)(m >> 32)), "s"(c));
-  asm("v_add_co_u32_e64 %0, %1, %2, %3" : "=v"(w1), "=s"(c) : "v"((uint32_t)(lo >> 32)), "v"((uint32_t)m));
-  asm("v_addc_co_u32_e64 %0, %1, %2, %3, %4" : "=v"(w2), "=s"(d) : "v"((uint32_t)hi), "v"(mh), "s"(c));
-  asm("v_addc_co_u32_e64 %0, %1, 0, %2, %3" : "=v"(w3), "=s"(c) : "v"((uint32_t)(hi >> 32)), "s"(d));
+  uint32_t w1 = (uint32_t)(lo >> 32), w2 = (uint32_t)hi, w3 = (uint32_t)(hi >> 32), mh = (uint32_t)(m >> 32);
+  asm("v_add_co_u32_e64 %0, %4, %0, %6\n\t"
+      "s_nop 0\n\t"
+      "v_addc_co_u32_e64 %3, %5, 0, %3, %5\n\t"
+      "v_addc_co_u32_e64 %1, %4, %1, %3, %4\n\t"
+      "s_nop 1\n\t"
+      "v_addc_co_u32_e64 %2, %4, 0, %2, %4"
+      : "+v"(w1), "+v"(w2), "+v"(w3), "+v"(mh), "=&s"(d), "+s"(c)
+      : "v"((uint32_t)m));
+#else  // the same steps
+  const uint32_t c = __builtin_add_overflow(lo, (uint64_t)a0 * b0, &lo) ? 1 : 0;
+  const uint32_t mh = (uint32_t)(m >> 32) + c;
+  const uint64_t s1 = (lo >> 32) + (uint32_t)m, s2 = (uint64_t)(uint32_t)hi + mh + (s1 >> 32);
+  const uint32_t w1 = (uint32_t)s1, w2 = (uint32_t)s2, w3 = (uint32_t)(hi >> 32) + (uint32_t)(s2 >> 32);
+#endif
   acc.lo = (uint32_t)lo | ((uint64_t)w1 << 32);
   acc.hi = w2 | ((uint64_t)w3 << 32);
-#else
-  add128(acc, mul_wide(a, b));
-#endif
 }
 
 // a b / 2^64 rounded down, or one less: the low partial product and its carry
@@ -104,14 +119,17 @@ __host__ __device__ __forceinline__ void mac128(U128& acc, uint64_t a, uint64_t 
 __host__ __device__ __forceinline__ uint64_t mulhi64_under(uint64_t a, uint64_t b) {
   const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32);
   const uint32_t b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
-#ifdef __HIP_DEVICE_COMPILE__
-  uint64_t m = (uint64_t)a0 * b1, c;
-  asm("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(m), "=s"(c) : "v"(a1), "v"(b0));
+  uint64_t m = (uint64_t)a0 * b1;
   uint32_t ch;
-  asm("v_cndmask_b32_e64 %0, 0, 1, %1" : "=v"(ch) : "s"(c));
+#ifdef __HIP_DEVICE_COMPILE__
+  uint64_t c;
+  asm("v_mad_u64_u32 %0, %1, %3, %4, %0\n\t"
+      "s_nop 1\n\t"
+      "v_cndmask_b32_e64 %2, 0, 1, %1"
+      : "+v"(m), "=&s"(c), "=v"(ch)
+      : "v"(a1), "v"(b0));
 #else
-  uint64_t m;
-  const uint32_t ch = __builtin_add_overflow((uint64_t)a0 * b1, (uint64_t)a1 * b0, &m) ? 1 : 0;
+  ch = __builtin_add_overflow(m, (uint64_t)a1 * b0, &m) ? 1 : 0;
 #endif
   return (uint64_t)a1 * b1 + ((m >> 32) | ((uint64_t)ch << 32));
 }
