@@ -373,8 +373,8 @@ struct EncItem {
 // FFT passes and forward NTTs (from the signed integers).  The FFT's scratch is
 // the item's first output limb; the integers of at most 64 items per launch
 // take workspace, those of more (up to kMaxEnc) the caller's `spare` limbs.
-// own_fft: the FFT's scratch is workspace too (outputs that overlap slots),
-// and 32 items share a launch.  All items of a call have the same scale and
+// own_fft: the FFT's scratch is workspace too (buffers that overlap), and 32
+// items share a launch.  All items of a call have the same scale and
 // primes.  128 items a launch instead of 32: dense Set-A (N = 2^13) 6.73 -> 4.63
 // ms, its launches of 320 limbs having left two thirds of the chip idle; at
 // N = 2^16, where 32 fill it, no difference (nor did launches small enough for
@@ -1307,20 +1307,32 @@ static int encode_common(const ckks_params* P, int count, const ckks_encode_item
   if (need) *need = D.ws.peak;
   if (plan_only) return CKKS_OK;
   if (D.ws.peak > ws_bytes || (D.ws.peak > 0 && !ws)) return CKKS_E_WORKSPACE;
-  // an output may hold slots that are still to be read (in place, or another
-  // item's): then no output serves as scratch
-  std::vector<std::pair<const uint8_t*, const uint8_t*>> in, out;
+  // Buffers of the call that share bytes: an output may hold slots that are still
+  // to be read, be another item's output too (a caller that wants only the
+  // integers), or hold integers.  Then no output serves as scratch, and the items
+  // run 32 a launch, in order.  (Slots may share bytes with slots: they are read.)
+  struct Span {
+    const uint8_t *lo, *hi;
+    bool slots;
+  };
+  std::vector<Span> spans;
+  const size_t limb = (size_t)P->n * 8;
+  auto span = [&](const void* at, size_t bytes, bool slots) {
+    const uint8_t* lo = static_cast<const uint8_t*>(at);
+    if (lo) spans.push_back(Span{lo, lo + bytes, slots});
+  };
   for (const EncItem& it : its) {
-    const uint8_t *z = reinterpret_cast<const uint8_t*>(it.z), *o = reinterpret_cast<const uint8_t*>(it.out);
-    in.push_back({z, z + (size_t)P->n * 8});
-    out.push_back({o, o + (size_t)n_limbs * P->n * 8});
+    span(it.z, limb, true);
+    span(it.out, n_limbs * limb, false);
+    span(it.coef, limb, false);
   }
-  std::sort(in.begin(), in.end());
-  std::sort(out.begin(), out.end());
+  std::sort(spans.begin(), spans.end(), [](const Span& x, const Span& y) { return x.lo < y.lo; });
   bool shared = false;
-  for (size_t i = 0, o = 0; i < in.size() && o < out.size() && !shared;) {
-    shared = in[i].first < out[o].second && out[o].first < in[i].second;
-    in[i].second < out[o].second ? ++i : ++o;
+  const uint8_t *read_to = nullptr, *written_to = nullptr;  // the ends of what came before
+  for (const Span& x : spans) {
+    shared = shared || x.lo < written_to || (!x.slots && x.lo < read_to);
+    const uint8_t*& to = x.slots ? read_to : written_to;
+    to = std::max(to, x.hi);
   }
   Run X = make_run(P, stream, false, ws);
   encode(X, its, {}, shared);
