@@ -153,7 +153,7 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
       uint64_t W[8], WP[8];
 #pragma unroll
       for (int y = 0; y < (1 << s); ++y) twid(s, (uint32_t)y, W[y], WP[y]);
-      F.stage_begin(k);
+      F.stage_begin(k, d);
 #pragma unroll
       for (int u = 0; u < 16; ++u)
         if (!(u & d)) F.bfly(u, d, W[u >> (4 - s)], WP[u >> (4 - s)]);
@@ -172,7 +172,7 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
       uint64_t W[8], WP[8];
 #pragma unroll
       for (int c = 0; c < (16 >> sh); ++c) twid(s, y0 + (uint32_t)c, W[c], WP[c]);
-      F.stage_begin(k - 4);
+      F.stage_begin(k - 4, d);
 #pragma unroll
       for (int u = 0; u < 16; ++u)
         if (!(u & d)) F.bfly(u, d, W[u >> sh], WP[u >> sh]);
@@ -372,7 +372,7 @@ __device__ __forceinline__ void full_stages(Butterflies<FP, FWD, (1 << LW)>& F, 
     FullTwiddles<LW> T1;
     full_twiddles<LOGN, LW, FWD, FP, I1, J1>(T1, tw, t);
     __builtin_amdgcn_sched_barrier(0);
-    F.stage_begin(J);
+    F.stage_begin(J, d);
 #pragma unroll
     for (int u = 0; u < (1 << LW); ++u)
       if (!(u & d)) F.bfly(u, d, T.w[u >> (bp + 1)], T.wp[u >> (bp + 1)]);

@@ -95,11 +95,11 @@ static long wrong(const Ring& R, const std::vector<int64_t>& in, bool is_signed,
   for (int k = 0; k < R.log_n; ++k) {
     const int st = FWD ? k : R.log_n - 1 - k, d = n >> (st + 1);
     const bool last = k + 1 == R.log_n || (k + 1) % round == 0;
-    F.stage_begin(k % round);
     for (int y = 0; y < 1 << st; ++y)
       for (int x = 2 * d * y; x < 2 * d * y + d; ++x) {
         const uint64_t tw = FWD ? R.w[(1 << st) + y] : R.iw[(1 << st) + y];
         F.v[0] = v[x], F.v[1] = v[x + d];
+        F.stage_begin(k % round, 1);
         F.bfly(0, 1, tw, FWD ? R.wp[(1 << st) + y] : R.iwp[(1 << st) + y]);
         F.stage_end(k % round, last, 1);
         if (last && k + 1 < R.log_n) F.recentre();
