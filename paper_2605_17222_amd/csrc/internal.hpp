@@ -34,10 +34,11 @@ struct PrimeDev {
   uint64_t r_lo, r_hi;     // floor(2^128 / q) (Barrett)
   uint64_t ninv, ninv_sh;  // N^-1 mod q and its Shoup companion
   uint64_t pmod, pmod_sh;  // P mod q (0 on the special primes) and companion
-  const uint64_t* tw;      // [4][N]: psi^br(i), Shoup, psi^-br(i), Shoup (integer primes) or
-                           // the same powers as doubles and each divided by q (fp primes)
-  const double* trow;      // fp primes: row-pass twiddle factors, [2][row_tables_size] (forward,
-                           // inverse); see ntt_row_tables_size
+  const uint64_t* tw;      // twiddles, [2][ntt_twiddle_words] (forward, inverse): the powers
+                           // psi^+-br(i), then on integer primes their Shoup words; as
+                           // doubles on fp primes
+  const double* trow;      // fp primes of the two-pass transforms: row-pass twiddle factors,
+                           // [2][row_tables_size] (forward, inverse); see ntt_row_tables_size
   int fp;                  // q < 2^46: NTT butterflies in exact FP64 arithmetic
   int pad;
   double qd, qinv_d;       // q and 1/q as doubles
@@ -75,6 +76,14 @@ __host__ __device__ inline int ntt_row_log(int log_n) { return log_n / 2; }
 __host__ __device__ inline size_t ntt_row_tables_size(int log_n) {
   const int B = ntt_row_log(log_n);
   return ((size_t)1 << B) + 2 * ((size_t)1 << (log_n - B)) * B;
+}
+
+// Words of one direction's twiddles (PrimeDev::tw): N powers and their Shoup
+// words on integer primes; on fp primes the powers that a transform reads, all N
+// in one kernel, those of the column pass in two.
+__host__ __device__ inline size_t ntt_twiddle_words(int log_n, bool fp) {
+  if (!fp) return (size_t)2 << log_n;
+  return (size_t)1 << (ntt_one_kernel(log_n) ? log_n : log_n - ntt_row_log(log_n));
 }
 
 // Basis conversion eq. (3) from `ns` source limbs to `nd` destination limbs,
@@ -294,8 +303,8 @@ struct ckks_params {
   int L = 0, alpha = 0, dnum = 0;
   std::vector<uint64_t> primes;        // PQ order
   ckks::PrimeDev* d_primes = nullptr;  // device [K_max]
-  uint64_t* d_tw = nullptr;            // device [K_max][4][N]
-  double* d_trow = nullptr;            // device [K_max][2][ntt_row_tables_size]
+  uint64_t* d_tw = nullptr;            // device: every prime's PrimeDev::tw
+  double* d_trow = nullptr;            // device: every PrimeDev::trow, or null (none)
   ckks::BConvPlan* d_plans = nullptr;  // device plan table
   uint64_t pk_poly_bytes = 0;          // bytes of one packed PQ polynomial (Kmax limbs)
   // Encoding tables (N/2 entries each): perm[j] = t with 5^t = 4 j + 1 mod 2N;

@@ -94,7 +94,7 @@ __device__ __forceinline__ void ntt_body(const LimbRange& R, int limb, const Pri
   Butterflies<FP, FWD> F(pr);
   uint64_t(&v)[16] = F.v;
   const int n = 1 << log_n;
-  const TableWords tw = (TableWords)(pr.tw + (FWD ? 0 : 2 * (size_t)n));
+  const TableWords tw = (TableWords)(pr.tw + (FWD ? 0 : ntt_twiddle_words(log_n, FP)));
   const bool first = (COL == FWD);  // first pass of the transform
   const uint64_t* __restrict__ src = (first ? R.in : R.out) + ((SIN && COL) ? 0 : (size_t)limb * n);
   uint64_t* __restrict__ dst = R.out + (size_t)limb * n;
@@ -404,7 +404,7 @@ __device__ __forceinline__ void ntt_full_body(const LimbRange& R, int limb, cons
 #pragma unroll
     for (int u = 0; u < (1 << LW); ++u) cp[at(u)] = v[u];
   }
-  const TableWords tw = (TableWords)(pr.tw + (FWD ? 0 : 2 * (size_t)n));
+  const TableWords tw = (TableWords)(pr.tw + (FWD ? 0 : ntt_twiddle_words(LOGN, FP)));
   FullTwiddles<LW> T;
   full_twiddles<LOGN, LW, FWD, FP, 0, 0>(T, tw, t);
   F.convert_in();

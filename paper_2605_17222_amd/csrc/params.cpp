@@ -175,9 +175,10 @@ int params_create(const ckks_params_desc* d, ckks_params** out) {
   if (hipGetDevice(&P->device) != hipSuccess) return CKKS_E_DEVICE;
 
   // psi and twiddle tables.
-  std::vector<uint64_t> tw((size_t)K * 4 * n);
+  std::vector<uint64_t> tw;
   const size_t rts = ntt_row_tables_size(P->log_n);
-  std::vector<double> trow((size_t)K * 2 * rts, 0.0);
+  std::vector<double> trow;
+  std::vector<size_t> tw_at(K), trow_at(K);
   std::vector<PrimeDev> pd(K);
   for (int i = 0; i < K; ++i) {
     const uint64_t q = P->primes[i];
@@ -191,7 +192,6 @@ int params_create(const ckks_params_desc* d, ckks_params** out) {
     }
     if (pw(psi, n, q) != q - 1) return CKKS_E_INVALID_ARG;  // not a primitive 2N-th root
     const uint64_t psi_inv = inv(psi, q);
-    uint64_t* t = tw.data() + (size_t)i * 4 * n;
     std::vector<uint64_t> pf(n), pi(n);
     uint64_t a = 1, b = 1;
     for (int k = 0; k < n; ++k) {
@@ -208,7 +208,9 @@ int params_create(const ckks_params_desc* d, ckks_params** out) {
         full_f[k] = pf[r];
         full_i[k] = pi[r];
       }
-      double* tr = trow.data() + (size_t)i * 2 * rts;
+      trow_at[i] = trow.size();
+      trow.resize(trow.size() + 2 * rts, 0.0);
+      double* tr = trow.data() + trow_at[i];
       if (!row_tables(q, psi, P->log_n, full_f.data(), tr) || !row_tables(q, psi_inv, P->log_n, full_i.data(), tr + rts))
         return CKKS_E_UNSUPPORTED;  // internal consistency check of the factorisation
     }
@@ -217,18 +219,17 @@ int params_create(const ckks_params_desc* d, ckks_params** out) {
       memcpy(&u, &x, 8);
       return u;
     };
-    for (int k = 0; k < n; ++k) {
-      const uint32_t r = brev(k, P->log_n);
-      if (fp) {
-        t[k] = dbits((double)pf[r]);
-        t[n + k] = dbits((double)pf[r] / (double)q);
-        t[2 * n + k] = dbits((double)pi[r]);
-        t[3 * n + k] = dbits((double)pi[r] / (double)q);
-      } else {
-        t[k] = pf[r];
-        t[n + k] = shoup_of(pf[r], q);
-        t[2 * n + k] = pi[r];
-        t[3 * n + k] = shoup_of(pi[r], q);
+    const size_t words = ntt_twiddle_words(P->log_n, fp);
+    tw_at[i] = tw.size();
+    tw.resize(tw.size() + 2 * words);
+    uint64_t *tf = tw.data() + tw_at[i], *ti = tf + words;
+    for (size_t k = 0; k < (fp ? words : (size_t)n); ++k) {
+      const uint32_t r = brev((uint32_t)k, P->log_n);
+      tf[k] = fp ? dbits((double)pf[r]) : pf[r];
+      ti[k] = fp ? dbits((double)pi[r]) : pi[r];
+      if (!fp) {
+        tf[n + k] = shoup_of(pf[r], q);
+        ti[n + k] = shoup_of(pi[r], q);
       }
     }
     PrimeDev& c = pd[i];
@@ -323,7 +324,7 @@ int params_create(const ckks_params_desc* d, ckks_params** out) {
 
   // Upload.
   if (hipMalloc(&P->d_tw, tw.size() * 8) != hipSuccess) return CKKS_E_NOMEM;
-  if (hipMalloc(&P->d_trow, trow.size() * 8) != hipSuccess) return CKKS_E_NOMEM;
+  if (!trow.empty() && hipMalloc(&P->d_trow, trow.size() * 8) != hipSuccess) return CKKS_E_NOMEM;
   if (hipMalloc(&P->d_primes, pd.size() * sizeof(PrimeDev)) != hipSuccess) return CKKS_E_NOMEM;
   for (const BConvPlan& pl : plans) {
     P->plan_shape.push_back({pl.ns, pl.nd});
@@ -334,11 +335,12 @@ int params_create(const ckks_params_desc* d, ckks_params** out) {
   if (hipMalloc(&P->d_enc_tw, etw.size() * 8) != hipSuccess) return CKKS_E_NOMEM;
   if (hipMalloc(&P->d_enc_zinv, ezinv.size() * 8) != hipSuccess) return CKKS_E_NOMEM;
   for (int i = 0; i < K; ++i) {
-    pd[i].tw = P->d_tw + (size_t)i * 4 * n;
-    pd[i].trow = P->d_trow + (size_t)i * 2 * rts;
+    pd[i].tw = P->d_tw + tw_at[i];
+    pd[i].trow = pd[i].fp && P->d_trow ? P->d_trow + trow_at[i] : nullptr;
   }
   if (hipMemcpy(P->d_tw, tw.data(), tw.size() * 8, hipMemcpyHostToDevice) != hipSuccess) return CKKS_E_DEVICE;
-  if (hipMemcpy(P->d_trow, trow.data(), trow.size() * 8, hipMemcpyHostToDevice) != hipSuccess) return CKKS_E_DEVICE;
+  if (!trow.empty() && hipMemcpy(P->d_trow, trow.data(), trow.size() * 8, hipMemcpyHostToDevice) != hipSuccess)
+    return CKKS_E_DEVICE;
   if (hipMemcpy(P->d_primes, pd.data(), pd.size() * sizeof(PrimeDev), hipMemcpyHostToDevice) != hipSuccess)
     return CKKS_E_DEVICE;
   if (hipMemcpy(P->d_plans, plans.data(), plans.size() * sizeof(BConvPlan), hipMemcpyHostToDevice) != hipSuccess)
