@@ -494,11 +494,10 @@ typedef struct {
 /*
  * Predicted device seconds of one LT with this split and n_diag present
  * diagonals: the operation counts of ckks_lt_cost_model priced with `rates`,
- * plus the words the key-switch and MAC kernels move in the schedule the rates
- * were fitted to (TH-BSGS with at most 4 accumulators, or 8 and at most 16
- * terms: the middle key switch fused with the multiply-accumulate, 16 terms a
- * launch, the rotation products never stored; the library itself fuses at
- * least those and in larger launches).  DH-BSGS (n1, n2) is priced as TH-BSGS (1, n1, n2).  The rates
+ * plus the words the key-switch and MAC kernels move as this library schedules
+ * one LT (TH-BSGS with at most 8 accumulators: the middle key switch fused with
+ * the multiply-accumulate, up to 64 terms a launch, the rotation products never
+ * stored).  DH-BSGS (n1, n2) is priced as TH-BSGS (1, n1, n2).  The rates
  * can be refitted on a device with `python -m paper_2605_17222_amd.calibrate`.
  */
 int ckks_lt_predict(int log_n, int level, int alpha, int algo, int n1, int n2, int n3, int n_diag,

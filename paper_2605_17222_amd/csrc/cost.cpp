@@ -24,6 +24,9 @@
 #include <algorithm>
 
 #include "../../include/ckks_lt.h"
+#include "internal.hpp"
+
+using namespace ckks;
 
 namespace {
 
@@ -108,16 +111,19 @@ int ckks_lt_predict(int log_n, int level, int alpha, int algo, int n1, int n2, i
   if (rates) {
     r = *rates;
   } else {
-    // Measured on one MI355X (python -m paper_2605_17222_amd.calibrate: 120
-    // banded LTs at N = 2^16, levels 8, 16, 24, 16..256 diagonals): the BConv
-    // rate from that kernel's own time, the other three fitted to the rest;
-    // mean prediction error 6.3% (max 20%), the pick 2.2% slower than the
-    // fastest timed split of its group on average (at most 7.4%; identical
-    // runs of one split differ by up to 2%).
-    r.ntt_limb_s = 1.82e-7;
-    r.bconv_product_s = 0.650e-12;
-    r.hbm_bytes_per_s = 4.69e12;
-    r.layer_s = 97.0e-6;
+    // Fitted on one MI355X to 224 banded LTs at N = 2^16 (levels 8, 16, 24; 16 to
+    // 512 diagonals, 1024 at level 24; for each the splits that several models
+    // rank first and a spread of others, timed as
+    // paper_2605_17222_amd.calibrate does), the BConv rate from that kernel's own
+    // time: mean prediction error 4.4% (max 24%), the pick 1.3% slower than the
+    // fastest timed split of its group on average (at most 5.1%; two runs of one
+    // split differ by 2%).  The other three rates are regression coefficients;
+    // among those that fit alike these keep the picks of the smaller diagonal
+    // counts that had been measured fastest.
+    r.ntt_limb_s = 3.03e-7;
+    r.bconv_product_s = 0.603e-12;
+    r.hbm_bytes_per_s = 5.89e12;
+    r.layer_s = 64.0e-6;
   }
   if (algo == CKKS_LT_DH_BSGS) {  // Algorithm 2 with an empty inner layer
     n3 = n2;
@@ -155,16 +161,13 @@ int ckks_lt_predict(int log_n, int level, int alpha, int algo, int n1, int n2, i
     conv += (double)gs * (K - gs);
   }
   const double bconv_products = (c.decompose * conv + c.moddown * alpha * Lq) * N;
-  // Words moved per coefficient position by the HBM-bound kernels in the
-  // schedule that the default rates were fitted to (the library now also fuses
-  // 5 to 8 accumulators with more terms, and runs up to 64 terms a launch; the
-  // model is kept with its rates, so that splits are chosen as before): a key (2 beta K words at this level) is read
+  // Words moved per coefficient position by the HBM-bound kernels as this
+  // library schedules one LT: a key (2 beta K words at this level) is read
   // once per launch for every digit set that uses it (up to 8 digit sets per
-  // launch).  With at most 4 accumulators, or at most 8 and terms that fit
-  // one launch, the middle key switch runs fused with the multiply-
-  // accumulate (lines 8-14 in one kernel per 16 terms): each middle key,
-  // digit set and add read once, the rotation products never stored;
-  // otherwise every product is written once and read once by the MAC.
+  // launch).  With at most 8 accumulators the middle key switch runs fused with
+  // the multiply-accumulate (lines 8-14 in one kernel per launch table of terms,
+  // keys and plaintexts): the rotation products are never stored; with more,
+  // every product is written once and read once by the MAC.
   const double keyw = 2.0 * beta * K;
   double words = 0;
   int layers = 0;
@@ -173,13 +176,22 @@ int ckks_lt_predict(int log_n, int level, int alpha, int algo, int n1, int n2, i
       words += beta * K + (n1 - 1) * keyw + (n1 - 1) * 2.0 * K + Lq;
       ++layers;
     }
-    if (n2 > 1 && n3 <= 8 && (n3 <= 4 || n1 * n2 <= 16)) {
-      // launches of 16 terms, ordered by middle step: each launch reads the
-      // digit sets and adds of its terms (up to 16) and each key once, and
-      // every launch after the first reads and writes the accumulators
-      const int launches = (n1 * n2 + 15) / 16, per = std::min(n1, 16), spans = (n1 + 15) / 16;
-      words += (double)spans * (n2 - 1) * keyw + (double)launches * per * (beta + 1.0) * K + 2.0 * n1 * K +
-               (double)n_diag * K + 2.0 * n3 * K + (launches - 1) * 4.0 * n3 * K;
+    if (n2 > 1 && n3 <= kMaxMacK) {
+      // terms ordered by middle step, n1 to a key and the first n1 unrotated: a
+      // launch takes as many as its tables hold, reads each of its keys once
+      // (one that ends inside a rotation's terms has the next read that key
+      // again), and, after the first, the accumulators too.  The digit sets and
+      // adds that its later rotations gather again come from L2 but take the
+      // path that bounds the kernel: they count a quarter (0.2 to 0.33 fit the
+      // measured times alike; not counted, the error is 5.3% instead of 4.6%,
+      // counted in full 6%)
+      const long cap = std::min(kMaxKsTerms, kMaxKsPts / n3);
+      const long first = std::min(cap, (kMaxKsKeys + 1L) * n1), next = std::min(cap, (long)kMaxKsKeys * n1);
+      const long launches = 1 + (std::max((long)n1 * n2 - first, 0L) + next - 1) / next;
+      const long again = first % n1 || next % n1 ? launches - 1 : 0;
+      const double sets = (double)launches * std::min<long>(n1, cap), gathered = n1 * (n2 - 1.0);
+      words += (n2 - 1.0 + again) * keyw + (sets + std::max(gathered - sets, 0.0) / 4) * (beta + 1.0) * K +
+               2.0 * n1 * K + (double)n_diag * K + (2.0 * launches - 1) * 2.0 * n3 * K;
       ++layers;
     } else {
       if (n2 > 1) {
