@@ -74,7 +74,8 @@ struct Butterflies {
   // inverse's cy, and the forward's operands that have to be reduced, all at once:
   // a test of the class in each butterfly kept the compiler from overlapping them
   // (one limb forward, a 60-bit prime at N = 2^14: 15.7 -> 12.8 us a call; 34 limbs at
-  // N = 2^15: 22.8 -> 19.9).  After it: the inverse's sums that have to be reduced.
+  // N = 2^15: 22.8 -> 19.9; column pass of 128 plaintexts of 44 54-bit limbs 1.14 ->
+  // 0.99 ms).  After it: the inverse's sums that have to be reduced.
   __host__ __device__ __forceinline__ void stage_begin(int k, int d) {
     if (!FP && !FWD) cy = q3 << (lazy == kFree ? k : (lazy == kRounds ? k & 1 : 0));
     if (!FP && FWD && lazy == kStages) {

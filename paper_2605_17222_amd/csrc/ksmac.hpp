@@ -134,8 +134,9 @@ struct KsMacFoldFp {
   __device__ __forceinline__ void rotated(const KsMacTerm<NK, MB>& o, bool pscaled) {
     double u = u64_to_d(o.a), v = 0.0;
     if (pscaled) u = fp_mulmod(u, pm, pmq, qd);
-    // not reduced: |u| < 0.6 beta q + q <= 3.4 q, within the 4 q that
-    // fp_mulmod_var takes for its first operand
+    // not reduced: |u| < 0.6 beta q + q <= 3.4 q, well within the 16 q that
+    // fp_mulmod_var takes for its first operand, and below 4 q, so that the
+    // products stay within 0.6 q
 #pragma unroll
     for (int b = 0; b < MB; ++b) {
       const double d = u64_to_d(o.d[b]);

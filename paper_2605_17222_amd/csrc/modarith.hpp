@@ -84,7 +84,8 @@ __host__ __device__ __forceinline__ uint64_t barrett128(U128 x, uint64_t q, uint
 
 // acc += a b for a, b < 2^61 (the cross products' sum stays below 2^63):
 // four multiply-adds and one carry chain, against fifteen instructions for
-// mul_wide and add128.
+// mul_wide and add128 (the waits cost nothing measurable: (4,4,4) at N = 2^16,
+// level 24 397 us fused with and without them).
 __host__ __device__ __forceinline__ void mac128(U128& acc, uint64_t a, uint64_t b) {
   const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32);
   const uint32_t b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);

@@ -23,10 +23,10 @@
 //  * integer (q >= 2^46): lazy butterflies with Shoup twiddle products whose
 //    quotient may be one short (mulhi64_under), so a product is in [0, 3q);
 //    values grow within 64 bits and are reduced as seldom as the prime's size
-//    allows (see Lazy below): about 16 instructions a butterfly against 29 with
-//    an exact quotient and a conditional subtraction (32 plaintexts of 44
-//    54-bit limbs at N = 2^16: column pass 401 -> 304 us, row pass 476 -> 397,
-//    with its twiddles from L2);
+//    allows (see Lazy in butterflies.hpp): about 16 instructions a butterfly
+//    against 29 with an exact quotient and a conditional subtraction (32
+//    plaintexts of 44 54-bit limbs at N = 2^16: column pass 401 -> 244 us, row
+//    pass 476 -> 371, its twiddles from L2);
 //  * FP64 (q < 2^46): residues are doubles holding exact integers, the
 //    twiddle product is the exact FMA two-product remainder of modarith.hpp,
 //    values are re-centred every 4 stages.  Between the two passes such a limb
@@ -35,7 +35,7 @@
 // Stage s of a sub-transform of P = 2^p points whose global twiddle base is B
 // uses twiddle index B 2^s + (x >> (p - s)) for butterfly position x; B = 1
 // for the column pass and B = N1 + row for the row pass.  The column pass
-// reads its 2^p - 1 twiddles from the full table (shared by all columns, so
+// reads its 2^p - 1 twiddles from the table (shared by all columns, so
 // they stay in cache); the row pass of an FP64 limb would read a different
 // 2^p - 1 for every row (the whole table, twice the limb's own bytes), so it
 // forms them instead as G[s][y] R[row][s] mod q from two small tables (the
@@ -284,12 +284,13 @@ __global__ void __launch_bounds__(G*(1 << PLOG) / 16) __attribute__((amdgpu_wave
 }
 
 // ---- N <= 2^13: a whole transform in one workgroup ---------------------------
-// A limb of at most 2^13 words (64 KiB, 68 KiB padded) leaves room for two
+// A limb of at most 2^13 words (64 KiB, 68 or 72 KiB padded) leaves room for two
 // workgroups in a CU's LDS, so all its stages run in one kernel of N / 16
-// threads (N / 8 for small launches): rounds of at most 4 stages in registers
-// with an LDS exchange between them, half the launches and half the memory
-// traffic of two passes: (2,2,4) at N = 2^12 168 -> 117 us, the encoded
-// plaintexts' forward passes of the dense LT at N = 2^13 4.84 -> 3.76 ms.  Bound
+// threads (N / 8 at N = 2^12 and for small launches): rounds of at most 4 stages
+// in registers with an LDS exchange between them, half the launches and half the
+// memory traffic of two passes: (2,2,4) at N = 2^12 168 -> 117 us, the encoded
+// plaintexts' forward passes of the dense LT at N = 2^13 4.84 -> 3.76 ms (2.05 now,
+// with 128 plaintexts a launch and no test in the butterflies).  Bound
 // by latency (few waves per SIMD) and VALU issue.  (At N = 2^14 a workgroup
 // would take a whole CU, and a launch of a few dozen limbs a few dozen CUs:
 // measured slower, 208 -> 276 us of forward passes at (4,4,8), level 22.)
@@ -479,7 +480,7 @@ hipError_t launch_both(const ckks_params* P, bool forward, const NttArgs& a, int
 // Row passes of encoded plaintexts over integer-path primes are taken prime by
 // prime, not item by item: such a pass reads twice as many twiddle words as
 // data words, and this way they come from L2 after the first item (44 limbs of
-// 54 bits x 32 plaintexts at N = 2^16: 369 -> 325 us; FP64-path limbs read small
+// 54 bits x 32 plaintexts at N = 2^16: 416 -> 371 us; FP64-path limbs read small
 // tables and are better off item by item, as are column passes, whose input all
 // limbs of an item share).
 template <int PA, int PB>
@@ -504,11 +505,12 @@ hipError_t launch_full(const ckks_params* P, const NttArgsOf<SIN>& a, int total,
   return hipGetLastError();
 }
 
-// Words per thread of the one-kernel transforms: a launch of at most a limb per
-// CU is bound by one workgroup's latency, so its limbs are spread over more
-// waves (8 words a thread against 16: 16 -> 12 us a transform of 2^12, 20 -> 18
-// us of 2^13); larger ones run faster with fewer exchanges (1280 limbs of 2^13:
-// 33 -> 29 us per 320).
+// Words per thread of the one-kernel transforms: 8 at N = 2^12 (16 against 8: one
+// limb 12.4 -> 10.0 us, 640 limbs 28.7 -> 21.1, 2176 limbs 47 -> 42).  At N = 2^13 a
+// launch of at most a limb per CU is bound by one workgroup's latency, so its
+// limbs are spread over more waves too (one limb 16.3 -> 14.3, 250 limbs 22.5 ->
+// 18.7); larger ones run faster with the fewer exchanges of 16 words (8 against 16:
+// 260 limbs alike, 640 43.0 -> 40.9, 2176 109 -> 92).
 template <bool FWD, bool SIN>
 hipError_t launch_one_kernel(const ckks_params* P, const NttArgsOf<SIN>& a, int total, double words, int epi,
                              hipStream_t s) {
