@@ -75,11 +75,10 @@ __host__ __device__ __forceinline__ uint64_t barrett128(U128 x, uint64_t q, uint
   return csub(x.lo - qhat * q, q);
 }
 
-// Carries in inline assembly.  On gfx950 a vector instruction that reads a mask (a
-// carry, a select) has to come at least two wait states after the vector
-// instruction that wrote it.  The compiler keeps that distance between its own
-// instructions but does not look into asm statements (between two of them it left
-// one, or none), so a mask is read in the statement that wrote it, with the
+// Carries in inline assembly.  On gfx950 the compiler keeps at least two wait states
+// between a vector instruction that writes a mask (a carry, a select) and one that
+// reads it, but it does not look into asm statements: between two of them it left
+// one, or none.  So a mask is read in the statement that wrote it, with that
 // distance kept there, or in a later one behind two wait states of its own.
 
 // acc += a b for a, b < 2^61 (the cross products' sum stays below 2^63):

@@ -7,8 +7,8 @@ import subprocess
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 NATIVE = os.path.join(ROOT, "tests", "native")
-# the wait states that a vector instruction reading a mask (carry, select) needs
-# after the vector instruction that wrote it
+# the wait states that the compiler keeps on gfx950 between a vector instruction that
+# writes a mask (carry, select) and one that reads it
 MASK_WAIT = 2
 
 
